@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libclearmoe.so")
 BUILD_DIR = os.path.join(ROOT, "_build", "clearmoe")
-SOURCES = ["api.cpp", "route.hip", "dispatch.hip", "gemm.hip", "fused.hip", "fused_split.hip",
+SOURCES = ["api.cpp", "route.hip", "dispatch.hip", "gemm.hip", "gemm_bf16.hip", "fused.hip", "fused_split.hip",
            "fused_cls.hip", "class_ffn.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

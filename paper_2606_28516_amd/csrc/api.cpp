@@ -491,7 +491,7 @@ int residual_impl(const clearmoe_shape& s, int64_t M, const void* z, const int32
                   const int32_t* seg, const float* gate, const void* P, const void* Q, void* u,
                   float* hres, hipStream_t st) {
     GemmDesc g = gemm_desc(M, s.q, s.H);
-    g.A = z; g.lda = s.H; g.a_rows = rows; g.a_div = s.k;
+    g.A = z; g.lda = s.H; g.a_rows = rows; g.a_div = s.k; g.a_nrows = s.T;
     g.B = Q; g.ldb = s.H; g.b_seg_stride = static_cast<int64_t>(s.q) * s.H;
     g.C = u; g.ldc = s.q; g.c_f32 = 0;
     g.row_scale = gate; g.scale_rows = rows;
@@ -873,7 +873,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
         void* tu = at<void>(ws, L.tu);
         const int rq = s.r + s.q;
         g = gemm_desc(A, rq, s.H);
-        g.A = z; g.lda = s.H; g.a_rows = perm; g.a_div = 1;
+        g.A = z; g.lda = s.H; g.a_rows = perm; g.a_div = 1; g.a_nrows = T;
         g.B = Vt; g.ldb = s.H; g.b_seg_stride = 0;
         g.B1 = Q; g.ldb1 = s.H; g.b1_seg_stride = static_cast<int64_t>(s.q) * s.H;
         g.n_split = s.r;
@@ -940,7 +940,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
                                              at<float>(ws, L.fpart), at<int32_t>(ws, L.fcount), st));
             // two-expert tokens: fc1 + GELU on their rows only, z in pair order
             g = gemm_desc(T, s.H, s.D);
-            g.A = x; g.lda = s.D; g.a_rows = pperm; g.a_div = 1;
+            g.A = x; g.lda = s.D; g.a_rows = pperm; g.a_div = 1; g.a_nrows = T;
             g.B = W1; g.ldb = s.D;
             g.C = z; g.ldc = s.H; g.c_f32 = 0;
             g.bias = b1; g.gelu = 1;
@@ -961,7 +961,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
                 void* tu = at<void>(ws, L.tu);
                 const int rq = s.r + s.q;
                 g = gemm_desc(T, rq, s.H);
-                g.A = z; g.lda = s.H; g.a_rows = pperm; g.a_div = 1;
+                g.A = z; g.lda = s.H; g.a_rows = pperm; g.a_div = 1; g.a_nrows = T;
                 g.B = Vt; g.ldb = s.H;
                 g.B1 = Q; g.ldb1 = s.H; g.b1_seg_stride = static_cast<int64_t>(s.q) * s.H;
                 g.n_split = s.r;
@@ -991,7 +991,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
         g = gemm_desc(T, rqq, s.H);
         g.A = z; g.lda = s.H;
         if (!z_pair_order) {
-            g.a_rows = pperm; g.a_div = 1;
+            g.a_rows = pperm; g.a_div = 1; g.a_nrows = T;
         }
         g.B = Vt; g.ldb = s.H;
         g.B1 = Q; g.ldb1 = s.H; g.b1_seg_stride = static_cast<int64_t>(s.q) * s.H;

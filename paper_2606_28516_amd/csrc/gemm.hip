@@ -571,32 +571,10 @@ static hipError_t gemm_cfg(const GemmDesc& g, hipStream_t st) {
 // wave's waits overlap the other's MFMAs).
 template <typename Tin>
 static hipError_t gemm_dt(const GemmDesc& g, hipStream_t st) {
-    const int64_t mt128 = (g.M + 127) / 128;
     if constexpr (sizeof(Tin) == 2) {
-        // bfloat16, measured on the DeiT-Base layer's products (50432 rows):
-        // 64-byte stages, three in flight, and two workgroups per CU (72 KB
-        // of LDS each) beat 128-byte stages two deep, which leave the loads'
-        // latency exposed (fc1 + GELU 446 -> 407 us, the dense fc2 320 ->
-        // 302); 256x128 over eight waves then beat every other tile of that
-        // kind for the long products with N >= 512 (the pair y product, N =
-        // 768, K = 384: 67 -> 58 us against 128x256) and for the long-K ones
-        // with 128 < N <= 512 (the pair [t|u_a|u_b] product, N = 384, K =
-        // 3072: 180 -> 173 us against 128x128 over four waves)
-        const int64_t mnk = g.M * static_cast<int64_t>(g.N) * g.K;
-        if (g.N >= 512 && (mnk >= (int64_t{1} << 35) || g.M >= 16384))
-            return gemm_cfg<Tin, 256, 128, 4, 2, 3, 64>(g, st);
-        if (g.N > 128 && g.N <= 512 && g.K >= 1024 && g.M >= 16384)
-            return gemm_cfg<Tin, 256, 128, 4, 2, 3, 64>(g, st);
-        if (g.N >= 1024 && g.K <= 512) return gemm_cfg<Tin, 128, 128, 4, 2, 2>(g, st);
-        // long k rows (2 KB or more) over a few hundred 64x64 tiles (e.g. the
-        // pair products of an adaptive layer at DeiT-Small widths, 28 -> 20
-        // us): four stages in flight; with more tiles, 128x128 over 8 waves
-        // (the DeiT-Small dense fc2, 35 -> 32 us)
-        if (g.K >= 1024 && g.N > 128 && g.N <= 512) {
-            const int64_t t64 = ((g.M + 63) / 64 + (g.seg_offsets != nullptr ? g.nseg : 0)) * ((g.N + 63) / 64);
-            if (t64 <= 1024) return gemm_cfg<Tin, 64, 64, 2, 2, 4>(g, st);
-            return gemm_cfg<Tin, 128, 128, 4, 2, 2>(g, st);
-        }
+        // bfloat16: only what gemm_bf16_supported leaves, operands of 2 GiB and
+        // more; 256x128 tiles with 64-byte stages for all but narrow products
+        if (g.N > 128) return gemm_cfg<Tin, 256, 128, 4, 2, 3, 64>(g, st);
     }
     if (g.N >= 1024 && ((g.M + 255) / 256) * ((g.N + 255) / 256) >= 1024)
         return gemm_cfg<Tin, 256, 256, 4, 2, 2>(g, st);
@@ -605,12 +583,14 @@ static hipError_t gemm_dt(const GemmDesc& g, hipStream_t st) {
     // long k rows (2 KB or more: a float32 stage holds half the k of a bf16 one)
     const int64_t kbytes = static_cast<int64_t>(g.K) * static_cast<int64_t>(sizeof(Tin));
     if (g.N <= 128 && kbytes >= 2048) return gemm_cfg<Tin, 64, 64, 2, 2, 4>(g, st);
+    const int64_t mt128 = (g.M + 127) / 128;
     if (mt128 * ((g.N + 127) / 128) < 2048) return gemm_cfg<Tin, 64, 128, 2, 2, 2>(g, st);
     return gemm_cfg<Tin, 128, 128, 2, 2, 2>(g, st);
 }
 
 hipError_t launch_gemm(int dtype, const GemmDesc& g, hipStream_t st) {
     if (dtype == 0) return gemm_dt<float>(g, st);
+    if (gemm_bf16_supported(g)) return launch_gemm_bf16(g, st);
     return gemm_dt<bf16_bits>(g, st);
 }
 

@@ -252,6 +252,7 @@ struct GemmDesc {
     const void* A;            // [*, K] in dtype, row stride lda (elements)
     int64_t lda;
     const int32_t* a_rows;    // optional gather: A row = a_rows[m] / a_div
+    int64_t a_nrows;          // with a gather: rows of A (0 = not stated)
     int a_div;
     const void* B;            // part 0: [N, K] per segment, row stride ldb
     int64_t ldb;
@@ -308,6 +309,10 @@ inline GemmDesc gemm_desc(int64_t M, int N, int K) {
     return g;
 }
 hipError_t launch_gemm(int dtype, const GemmDesc& g, hipStream_t st);
+// The bfloat16 products' own kernels (gemm_bf16.h), which launch_gemm uses
+// where they apply.
+bool gemm_bf16_supported(const GemmDesc& g);
+hipError_t launch_gemm_bf16(const GemmDesc& g, hipStream_t st);
 
 // Fused top-1 layer in bfloat16: y[perm p] = [t|u](p) [US | P_e]^T + b2 with
 // [t|u](p) = GELU(x[perm p] W1^T + b1) [Vt ; Q_e]^T (u columns times the gate),
