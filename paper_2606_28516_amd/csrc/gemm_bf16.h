@@ -49,6 +49,15 @@ __device__ __forceinline__ gb_i32x4 gb_desc(const void* p, int64_t bytes) {
     return d;
 }
 
+// Descriptor of part 0, 1 or 2 (uniform), chosen word by word: an index into
+// an array of descriptors would go through scratch memory.
+__device__ __forceinline__ gb_i32x4 gb_pick(const gb_i32x4& d0, const gb_i32x4& d1, const gb_i32x4& d2, int part) {
+    gb_i32x4 d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = __builtin_amdgcn_readfirstlane(part == 0 ? d0[i] : part == 1 ? d1[i] : d2[i]);
+    return d;
+}
+
 // 16 bytes per lane, buffer -> LDS at m0 + 16 * lane.  Inline asm: the
 // compiler does not count these loads, the pipeline's explicit waits do.
 __device__ __forceinline__ void gb_dma16(const gb_i32x4& d, uint32_t voff, uint32_t soff, uint32_t m0) {
@@ -405,14 +414,13 @@ void k_gemm_bf16(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
     auto dma = [&](int kt, int b, int i) {
         // first k of the stage in A and in the part of B, and k left there
         int ka = kt * BK, kb = ka, left = g.K - ka;
-        gb_i32x4 d = db[0];
-        bool part1 = false;
+        int part = 0;
         if constexpr (KS3) {
             left = k1 - ka;
             if (kt >= s2) {
-                kb = (kt - s2) * BK; ka = k2 + kb; left = g.K - ka; d = db[2]; part1 = true;
+                kb = (kt - s2) * BK; ka = k2 + kb; left = g.K - ka; part = 2;
             } else if (kt >= s1) {
-                kb = (kt - s1) * BK; ka = k1 + kb; left = k2 - ka; d = db[1]; part1 = true;
+                kb = (kt - s1) * BK; ka = k1 + kb; left = k2 - ka; part = 1;
             }
         }
         const bool cut = left < BK;                     // uniform: chunks past the end read zeros
@@ -426,8 +434,13 @@ void k_gemm_bf16(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
             const int q = i - AL < BL && i >= AL ? i - AL : 0;
             const int r = (wave * BL + q) * RPL + lr;
             uint32_t v = vb[q];
-            if constexpr (KS3) v = part1 ? vb1[q] : v;
-            else d = db[q];
+            gb_i32x4 d;
+            if constexpr (KS3) {
+                v = part > 0 ? vb1[q] : v;
+                d = gb_pick(db[0], db[1], db[2], part);
+            } else {
+                d = db[q];
+            }
             if (cut) v = chunk_k(r) < left ? v : kGbOob;
             gb_dma16(d, v, __builtin_amdgcn_readfirstlane(kb * 2),
                      __builtin_amdgcn_readfirstlane(lds0 + b * STAGE + STAGE_A + (wave * BL + q) * 1024));
@@ -656,6 +669,130 @@ void k_gemm_bf16_long(GemmDesc g, int mtiles, int ntiles, int group, int nt_stor
                              nt_store != 0, acc);
 }
 
+// fc1 + GELU over many rows: 256 x 128 tile over four waves (2 x 2, each 128 x
+// 64), two workgroups on a CU.  A tile's GELUs take about as many vector cycles
+// as its k loop takes matrix cycles at K = 768 (80 each, four of a wave's
+// instructions being quarter rate), and its rows a third of the time in
+// stores; a single workgroup of the tiles above has nothing to run beside
+// them, here one workgroup's epilogue runs beside the other's MFMAs.  80 KB of
+// LDS each: A has two stage buffers, B one, which is free as soon as its
+// fragments (a whole stage's, read first) are in registers.
+// 50432 x 3072 x 768 320 -> 268 us, 50432 x 1536 x 384 111 -> 93, 25216 x 3072
+// x 768 149 -> 138.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_gemm_bf16_duo(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
+    constexpr int SB = kGbRow, BM = 256, BN = 128, CPR = 8, BK = 64, TM = 4, TN = 2, AL = 8, BL = 4;
+    constexpr int ABUF = BM * SB, BOFF = 2 * ABUF;      // buffers A0 A1 B
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[BOFF + BN * SB];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int lrow = lane & 31, lh = lane >> 5;
+
+    GbTile t;
+    if (!gb_tile<BM>(g, mtiles, ntiles, group, lane, t)) return;
+    const int n0 = t.nt * BN;
+    const GbParts bp = gb_parts(g, t.seg);
+
+    const int lr = lane / CPR, cp = lane % CPR;
+    const gb_i32x4 da = gb_a_desc(g, t.m_lo, t.rows);
+    // first k of the lane's chunk in an even load's 8 rows; odd: ^ 32
+    const int kc0 = 8 * (cp ^ (lr >> 1));
+    uint32_t va[AL], vb[BL];
+    gb_i32x4 db[BL];
+#pragma unroll
+    for (int i = 0; i < AL; ++i)
+        va[i] = gb_a_offset(g, t.m_lo, t.rows, (wave * AL + i) * 8 + lr, kc0 ^ (32 * (i & 1)));
+#pragma unroll
+    for (int i = 0; i < BL; ++i)
+        vb[i] = gb_b_offset(g, bp, n0 + (wave * BL + i) * 8, n0 + (wave * BL + i) * 8 + lr, kc0 ^ (32 * (i & 1)),
+                            db[i]);
+    const int nk = (g.K + BK - 1) / BK, K = g.K;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((gb_lds_u32*)smem)));
+    auto masked = [&](uint32_t v, int kt, int i) {
+        if ((kt + 1) * BK > K) v = kt * BK + (kc0 ^ (32 * (i & 1))) < K ? v : kGbOob;
+        return v;
+    };
+    auto dma_a = [&](int kt, int b) {
+#pragma unroll
+        for (int i = 0; i < AL; ++i)
+            gb_dma16(da, masked(va[i], kt, i), __builtin_amdgcn_readfirstlane(kt * BK * 2),
+                     __builtin_amdgcn_readfirstlane(lds0 + b * ABUF + (wave * AL + i) * 1024));
+    };
+    auto dma_b = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < BL; ++i)
+            gb_dma16(db[i], masked(vb[i], kt, i), __builtin_amdgcn_readfirstlane(kt * BK * 2),
+                     __builtin_amdgcn_readfirstlane(lds0 + BOFF + (wave * BL + i) * 1024));
+    };
+    dma_a(0, 0);
+    dma_b(0);
+    f32x16 acc[TM][TN];
+    gb_init(g, n0 + wn * TN * 32, lh, acc);
+
+    const int bcol = gb_col_of_slot(lrow);
+    uint32_t oa[4], ob[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        oa[s] = static_cast<uint32_t>((wm * 128 + lrow) * SB + (((2 * s + lh) ^ gb_swz<SB>(lrow)) << 4));
+        ob[s] = static_cast<uint32_t>(BOFF + (wn * 64 + bcol) * SB + (((2 * s + lh) ^ gb_swz<SB>(bcol)) << 4));
+    }
+    u32x4 fa[2][TM], fb[4][TN];
+    auto read_a = [&](int b, int s) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            fa[s & 1][i] = *reinterpret_cast<const u32x4*>(smem + oa[s] + b * ABUF + i * 32 * SB);
+    };
+    auto mm = [&](int s) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8, fb[s][j]), __builtin_bit_cast(bf16x8, fa[s & 1][i]),
+                    acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int k0 = 0; k0 < nk; k0 += 2) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int kt = k0 + b;
+            if (kt >= nk) break;
+            // stage kt has landed for every wave, and every wave is done
+            // reading the other A buffer
+            gb_wait_barrier<0>();
+            if (kt + 1 < nk) dma_a(kt + 1, b ^ 1);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                fb[0][j] = *reinterpret_cast<const u32x4*>(smem + ob[0] + j * 32 * SB);
+            read_a(b, 0);
+#pragma unroll
+            for (int s = 1; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    fb[s][j] = *reinterpret_cast<const u32x4*>(smem + ob[s] + j * 32 * SB);
+            read_a(b, 1);
+            mm(0);
+            if (kt + 1 < nk) {
+                // every wave has read this stage's B
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                dma_b(kt + 1);
+            }
+            read_a(b, 2);
+            mm(1);
+            read_a(b, 3);
+            mm(2);
+            mm(3);
+        }
+    }
+    gb_wait_barrier<0>();                        // the stage buffers are free
+    gb_epilogue<TM, TN, kEpiGelu>(g, t, wm * TM * 32, n0 + wn * TN * 32, lane, smem + wave * (32 * TN * 64),
+                             nt_store != 0, acc);
+}
+
 template <int BM, int BN>
 bool gb_grid(const GemmDesc& g, int64_t& mt, int64_t& nt) {
     mt = (g.M + BM - 1) / BM;
@@ -686,6 +823,15 @@ hipError_t gemm_bf16_long(const GemmDesc& g, hipStream_t st) {
     if (!gb_grid<256, 256>(g, mt, nt)) return hipSuccess;
     const int64_t grid = (mt * nt + kGbXcds - 1) / kGbXcds * kGbXcds;
     launch_kernel(k_gemm_bf16_long<EPI>, dim3(static_cast<unsigned>(grid)), 512, 0, st, g,
+                  static_cast<int>(mt), static_cast<int>(nt), 4, gb_stream(g));
+    return hipGetLastError();
+}
+
+inline hipError_t gemm_bf16_duo(const GemmDesc& g, hipStream_t st) {
+    int64_t mt, nt;
+    if (!gb_grid<256, 128>(g, mt, nt)) return hipSuccess;
+    const int64_t grid = (mt * nt + kGbXcds - 1) / kGbXcds * kGbXcds;
+    launch_kernel(k_gemm_bf16_duo, dim3(static_cast<unsigned>(grid)), 256, 0, st, g,
                   static_cast<int>(mt), static_cast<int>(nt), 4, gb_stream(g));
     return hipGetLastError();
 }

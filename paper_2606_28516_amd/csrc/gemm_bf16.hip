@@ -53,6 +53,14 @@ int gb_stages(const GemmDesc& g) {
     return (k1 + BK - 1) / BK + (k2 - k1 + BK - 1) / BK + (g.K - k2 + BK - 1) / BK;
 }
 
+// fc1 + GELU with kGbDuoTiles tiles of 256 x 128 or more (three for each of the
+// 256 CUs, which hold two at a time): k_gemm_bf16_duo.  Measured against the
+// best of the tiles above, N = 768 .. 3072, K = N / 4: 0.96 of its time at
+// 900 tiles, 0.93 at 1200, 0.83 to 0.93 at 1200 to 4700, but 1.01 to 1.08
+// at 480 to 600 tiles (one full round and a small rest).
+constexpr int64_t kGbDuoTiles = 768;
+int64_t gb_gelu_tiles(const GemmDesc& g) { return ((g.M + 255) / 256) * ((g.N + 127) / 128); }
+
 template <int EPI, bool KS3>
 hipError_t gb_launch(const GemmDesc& g, hipStream_t st) {
     const int stages = gb_stages(g);
@@ -107,7 +115,8 @@ hipError_t launch_gemm_bf16(const GemmDesc& g, hipStream_t st) {
         if (g.gelu || g.row_scale != nullptr) return hipErrorInvalidValue;
         return gb_launch<kEpiPlain, true>(g, st);
     }
-    if (g.gelu) return gb_launch<kEpiGelu, false>(g, st);
+    if (g.gelu)
+        return gb_gelu_tiles(g) >= kGbDuoTiles ? gemm_bf16_duo(g, st) : gb_launch<kEpiGelu, false>(g, st);
     if (g.row_scale != nullptr) return gb_launch<kEpiScale, false>(g, st);
     return gb_launch<kEpiPlain, false>(g, st);
 }

@@ -1,0 +1,44 @@
+"""The bfloat16 GEMM's tiles (csrc/gemm_bf16.h) through the dense FFN, at the
+sizes where they can go wrong: one row, one tile and one more row, rows, widths
+and k that end inside a tile or a stage, and each tile's range of sizes."""
+import pytest
+import torch
+
+from paper_2606_28516_amd import clearmoe as cm
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [
+    # T, D (k of fc1, columns of fc2), H
+    (1, 8, 8),                # smallest
+    (64, 64, 64), (65, 72, 72),
+    (197, 384, 1536),
+    (320, 200, 1560),
+    (1000, 384, 1544),
+    (3152, 768, 3072),
+    (6304, 136, 1032),
+    (16384, 96, 1536),        # 768 tiles of 256 x 128: the two-workgroup fc1 tile
+    (16421, 96, 1528),        # ... with short last row and column tiles
+    (16129, 64, 1536),        # ... one k stage, one row in the last row tile
+    (8449, 320, 2944),        # ... an odd number of k stages
+    (8192, 1032, 3072),       # ... a last stage of 8 k
+]
+
+
+@pytest.mark.parametrize("T,D,H", SIZES)
+def test_dense_ffn_tiles(T, D, H):
+    g = torch.Generator(device="cuda").manual_seed(T * 31 + D)
+    n = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    x, W1, W2 = n(T, D).bfloat16(), (n(H, D) / D ** 0.5).bfloat16(), (n(D, H) / H ** 0.5).bfloat16()
+    b1, b2 = 0.1 * n(H), 0.1 * n(D)
+    y = cm.dense_ffn_forward(x, W1, b1, W2, b2).double()
+    z = torch.nn.functional.gelu(x.double() @ W1.double().T + b1.double())
+    ref = z @ W2.double().T + b2.double()
+    # y is rounded once (2^-9 of itself) from a sum over z rounded to bf16
+    # (2^-9 of each |z w|; twice that where the float32 z lands on the other
+    # side of a tie), plus float32 sums, far below either
+    bound = 2.0 ** -8 * (ref.abs() + z.abs() @ W2.double().abs().T) + 1e-6
+    assert (y - ref).abs().le(bound).all()
+    # the roundings are independent: over the whole result they stay near
+    # sqrt(2) 2^-9 / sqrt(3), well under 2^-8
+    assert ((y - ref).norm() / ref.norm()).item() <= 2.0 ** -8
