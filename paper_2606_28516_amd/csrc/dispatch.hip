@@ -147,81 +147,65 @@ __global__ __launch_bounds__(kRouteTile) void k_permute(
     const int64_t na64 = A - a0 < static_cast<int64_t>(kRouteTile) * k ? A - a0
                                                                          : static_cast<int64_t>(kRouteTile) * k;
     const int na = static_cast<int>(na64);
-    if (tile_counts != nullptr) {
-        if (tid < E) {
-            s_pre[tid] = 0;
-            s_tot[tid] = 0;
-        }
-        __syncthreads();
-        const int64_t nt = (T + htile - 1) / htile;
-        const int64_t first = static_cast<int64_t>(blockIdx.x) * (kRouteTile / htile);
-        // thread tid sums, for expert tid % E, the tiles tid / E + G i in
-        // registers (coalesced reads), then adds its two sums into LDS: one
-        // atomic per thread instead of one per histogram entry
-        const int G = kRouteTile / E;                  // threads per expert
-        if (tid < G * E) {
-            const int e = tid % E;
-            int tot = 0, pre = 0;
-            for (int64_t b = tid / E; b < nt; b += G) {
-                const int c = tile_counts[b * E + e];
-                tot += c;
-                pre += b < first ? c : 0;
+    // Rows of E counts to sum per expert: the histogram's tiles (inline scan)
+    // or the chunked scan's totals; those before `mine` precede this tile.
+    const bool inline_scan = tile_counts != nullptr;
+    const int32_t* rows = inline_scan ? tile_counts : chunk_tot;
+    const int64_t nrows = inline_scan ? (T + htile - 1) / htile : (route_tiles(T) + kScanChunk - 1) / kScanChunk;
+    const int64_t mine = inline_scan ? static_cast<int64_t>(blockIdx.x) * (kRouteTile / htile)
+                                     : static_cast<int64_t>(blockIdx.x) / kScanChunk;
+    if (tid < E) {
+        s_pre[tid] = 0;
+        s_tot[tid] = 0;
+        s_run[tid] = 0;
+    }
+    __syncthreads();
+    // thread tid sums, for expert tid % E, the rows tid / E + G i in
+    // registers (coalesced reads, eight in flight: one at a time cost 28 load
+    // latencies at 36 keys and 197 tiles), then adds its two sums into LDS:
+    // one atomic per thread instead of one per entry
+    const int G = kRouteTile / E;                      // threads per expert
+    if (tid < G * E) {
+        const int e = tid % E;
+        int tot = 0, pre = 0;
+        for (int64_t b0 = tid / E; b0 < nrows; b0 += 8 * G) {
+            int c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t b = b0 + u * G;
+                c[u] = b < nrows ? rows[b * E + e] : 0;
             }
-            atomicAdd(&s_tot[e], tot);
-            atomicAdd(&s_pre[e], pre);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            int o = 0;
-            for (int e = 0; e < E; ++e) {
-                s_base[e] = o + s_pre[e];
-                if (blockIdx.x == 0) {
-                    counts[e] = s_tot[e];
-                    offsets[e] = o;
-                }
-                o += s_tot[e];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                tot += c[u];
+                pre += b0 + u * G < mine ? c[u] : 0;
             }
+        }
+        atomicAdd(&s_tot[e], tot);
+        atomicAdd(&s_pre[e], pre);
+    }
+    __syncthreads();
+    if (w == 0) {
+        // offsets: prefix sum of the totals, lane e holding expert e (E <= 64)
+        const int tot = lane < E ? s_tot[lane] : 0;
+        int o = tot;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int n = __shfl_up(o, d);
+            if (lane >= d) o += n;
+        }
+        if (lane < E) {
+            s_base[lane] = o - tot + s_pre[lane] +
+                           (inline_scan ? 0 : tb[static_cast<int64_t>(blockIdx.x) * E + lane]);
+            if (blockIdx.x == 0) {
+                counts[lane] = tot;
+                offsets[lane] = o - tot;
+            }
+        }
+        if (lane == E - 1) {
             if (blockIdx.x == 0) offsets[E] = o;
             s_total = o;
         }
-        if (tid < E) s_run[tid] = 0;
-    } else {
-        // tile bases from the chunked scan: earlier chunks' totals plus the
-        // prefix within this tile's chunk; offsets from the grand totals
-        if (tid < E) {
-            s_pre[tid] = 0;
-            s_tot[tid] = 0;
-        }
-        __syncthreads();
-        const int64_t nchunks = (route_tiles(T) + kScanChunk - 1) / kScanChunk;
-        const int64_t mychunk = static_cast<int64_t>(blockIdx.x) / kScanChunk;
-        const int G = kRouteTile / E;
-        if (tid < G * E) {
-            const int e = tid % E;
-            int tot = 0, pre = 0;
-            for (int64_t c = tid / E; c < nchunks; c += G) {
-                const int v = chunk_tot[c * E + e];
-                tot += v;
-                pre += c < mychunk ? v : 0;
-            }
-            atomicAdd(&s_tot[e], tot);
-            atomicAdd(&s_pre[e], pre);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            int o = 0;
-            for (int e = 0; e < E; ++e) {
-                s_base[e] = o + s_pre[e] + tb[static_cast<int64_t>(blockIdx.x) * E + e];
-                if (blockIdx.x == 0) {
-                    counts[e] = s_tot[e];
-                    offsets[e] = o;
-                }
-                o += s_tot[e];
-            }
-            if (blockIdx.x == 0) offsets[E] = o;
-            s_total = o;
-        }
-        if (tid < E) s_run[tid] = 0;
     }
     __syncthreads();
     // Empty slots (index -1) are in no sub-batch: perm ends with -1 entries
@@ -264,38 +248,37 @@ __global__ __launch_bounds__(kRouteTile) void k_permute(
     }
     if (xperm != nullptr) {
         // Row copy: 16-byte pieces, eight per thread per round (all loads
-        // issued before the stores; measured against 4 and 16 at 2^20 tokens);
-        // the destination rows are written once and read later by another
-        // kernel, so the stores bypass the caches.
+        // issued before the stores; measured against 4 and 16 at 2^20 tokens).
+        // A piece of x is read once and stored at the token's k destinations;
+        // the rows are written once and read later by another kernel, so the
+        // stores bypass the caches.
         constexpr int PER16 = Elem<Tin>::per16;
         constexpr int U = 8;
         const int ppr = D / PER16;                      // 16-byte pieces per row
-        const int npairs = na * ppr;
-        for (int base = 0; base < npairs; base += U * kRouteTile) {
+        const int nt = na / k;                          // tokens of this tile
+        const int npieces = nt * ppr;
+        const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kRouteTile;
+        const u32x4* src = reinterpret_cast<const u32x4*>(x + t0 * D);
+        for (int base = 0; base < npieces; base += U * kRouteTile) {
             u32x4 v[U];
-            int dp[U], dc[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int pr = base + u * kRouteTile + tid;
-                dp[u] = -1;
-                dc[u] = 0;
-                if (pr < npairs) {
+                if (pr < npieces) v[u] = __builtin_nontemporal_load(src + pr);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int pr = base + u * kRouteTile + tid;
+                if (pr < npieces) {
                     const int al = pr / ppr, pc = pr - al * ppr;
-                    const int p = s_p[al];
-                    if (p >= 0) {
-                        const int64_t tok = (a0 + al) / k;
-                        v[u] = *reinterpret_cast<const u32x4*>(x + tok * D + pc * PER16);
-                        dp[u] = p;
-                        dc[u] = pc;
+                    for (int j = 0; j < k; ++j) {
+                        const int p = s_p[al * k + j];
+                        if (p >= 0)
+                            __builtin_nontemporal_store(
+                                v[u], reinterpret_cast<u32x4*>(xperm + static_cast<int64_t>(p) * D + pc * PER16));
                     }
                 }
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (dp[u] >= 0)
-                    __builtin_nontemporal_store(
-                        v[u], reinterpret_cast<u32x4*>(xperm + static_cast<int64_t>(dp[u]) * D +
-                                                       dc[u] * PER16));
         }
     }
 }
@@ -333,7 +316,7 @@ __global__ __launch_bounds__(256) void k_combine_gated(const T* __restrict__ ye,
                 const int64_t p = inv[t * k + j];
                 if (p >= 0 && p < A) {               // never follow an invalid index
                     g[u] = gate[t * k + j];
-                    v[u] = *reinterpret_cast<const u32x4*>(ye + p * D + pc * PER16);
+                    v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ye + p * D + pc * PER16));
                 }
             }
         }
@@ -356,7 +339,7 @@ __global__ __launch_bounds__(256) void k_combine_gated(const T* __restrict__ ye,
         u32x4 o;
         __builtin_memcpy(&o, out, 16);
         const int64_t t = pr / ppr, pc = pr - t * ppr;
-        *reinterpret_cast<u32x4*>(y + t * D + pc * PER16) = o;
+        __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(y + t * D + pc * PER16));
     }
 }
 
@@ -406,11 +389,8 @@ __global__ __launch_bounds__(256) void k_combine_residual(const float* __restric
         const int64_t pr = base + u * 256;
         if (pr >= n) continue;
         const int64_t t = pr / ppr, pc = pr - t * ppr;
-        T* dst = y + t * D + pc * 4;
-        dst[0] = Elem<T>::from_f32(a[u].x);
-        dst[1] = Elem<T>::from_f32(a[u].y);
-        dst[2] = Elem<T>::from_f32(a[u].z);
-        dst[3] = Elem<T>::from_f32(a[u].w);
+        const float o[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
+        Elem<T>::store4(y + t * D + pc * 4, o);
     }
 }
 
