@@ -674,6 +674,25 @@ int clearmoe_combine(const clearmoe_shape* shape, const void* ye, const int32_t*
 
 namespace {
 
+// Whether a layer's last kernel can add the layer's input to y: bfloat16, a
+// dense FFN or a CLEAR-MoE layer whose last kernel writes each y row once
+// (top-1, top-2 in pair order; where the fused kernel runs, its variant with
+// the class rows), and operands whose byte offsets fit the bfloat16 products'
+// descriptors (class rows are dense_stride rows apart).
+bool skip_in_layer(const clearmoe_shape& s, const clearmoe_router* rt) {
+    if (s.dtype != CLEARMOE_BF16) return false;
+    const int64_t stride = rt != nullptr ? rt->dense_stride : 0;
+    if (rt != nullptr) {
+        if (s.k != 1 && !pair_path(s)) return false;
+        if (fused_top1_supported(s.D, s.H, s.r, s.q) &&
+            (s.k == 1 ? stride == 0 || fused_split(s.T, s.E, s.H) > 1 || !class_ffn_supported(s.D, s.H)
+                      : rt->adaptive != 0))
+            return false;
+    }
+    const int64_t wide = s.H > s.D ? s.H : s.D, rows = wide > 512 ? wide : 512;
+    return stride <= (int64_t{1} << 20) && rows * wide * (stride > 1 ? stride : 1) < (int64_t{1} << 30);
+}
+
 // Class tokens (every dense_stride-th token, from token 0) on the dense path:
 // y[c] = GELU(x[c] W1^T + b1) W2^T + b2 over the ceil(T / dense_stride) class
 // rows, which the strided leading dimensions pick out of x and y.  With
@@ -682,7 +701,7 @@ namespace {
 // into the workspace's z region first.
 int class_tokens_impl(const clearmoe_shape& s, const clearmoe_router& rt, const void* x,
                       const void* W1, const float* b1, const float* b2, void* z, bool z_all,
-                      void* y, const Layout& L, void* ws, hipStream_t st) {
+                      void* y, const Layout& L, void* ws, bool add_x, hipStream_t st) {
     const int64_t sd = rt.dense_stride;
     const int64_t ncls = (s.T + sd - 1) / sd;
     int64_t zld = s.H;
@@ -699,6 +718,7 @@ int class_tokens_impl(const clearmoe_shape& s, const clearmoe_router& rt, const 
         c.stride = sd;
         c.D = s.D;
         c.H = s.H;
+        c.add_x = add_x ? 1 : 0;
         class_ffn_plan(c, at<float>(ws, L.cpart), at<uint64_t>(ws, L.ccount));
         CLEARMOE_STAGE(CLEARMOE_STAGE_DENSE_FC2, st, launch_class_ffn(c, st));
         return CLEARMOE_OK;
@@ -718,6 +738,9 @@ int class_tokens_impl(const clearmoe_shape& s, const clearmoe_router& rt, const 
     g.B = rt.W2; g.ldb = s.H;
     g.C = y; g.ldc = static_cast<int64_t>(s.D) * sd; g.c_f32 = 0;
     g.bias = b2;
+    if (add_x) {
+        g.res = x; g.ldr = static_cast<int64_t>(s.D) * sd;
+    }
     CLEARMOE_STAGE(CLEARMOE_STAGE_DENSE_FC2, st, launch_gemm(s.dtype, g, st));
     return CLEARMOE_OK;
 }
@@ -726,7 +749,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
                      const void* W1, const float* b1, const void* US, const void* Vt,
                      const float* b2, const void* P, const void* Q, void* y, int32_t* idx_out,
                      float* gate_out, void* ws, size_t ws_bytes, hipStream_t stream,
-                     const Layout* packed = nullptr) {
+                     const Layout* packed = nullptr, bool add_x = false) {
     int rc = check_layer_args(shape, x, W1, b1, US, Vt, b2, P, Q, nullptr, nullptr, y, idx_out,
                               gate_out);
     if (rc != CLEARMOE_OK) return rc;
@@ -734,6 +757,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
     rc = check_router(s, router);
     if (rc != CLEARMOE_OK) return rc;
     if (router->dense_stride > 0 && router->W2 == nullptr) return CLEARMOE_ERR_INVALID_ARG;
+    if (add_x && !skip_in_layer(s, router)) return CLEARMOE_ERR_INVALID_ARG;
     // a packed layout (no-allocation variant) serves only the linear router
     // without class tokens, whose regions it holds
     if (packed != nullptr && (router->hidden != 0 || router->adaptive || router->dense_stride > 0))
@@ -744,6 +768,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
 
     hipStream_t st = stream;
     const int64_t T = s.T, A = T * s.k;
+    const void* skip = add_x ? x : nullptr;    // the layer adds its input to y
     const bool cls = router->dense_stride > 0;
     const bool fused = s.k == 1 && s.dtype == CLEARMOE_BF16 && fused_top1_supported(s.D, s.H, s.r, s.q);
     int32_t* idx = idx_out ? idx_out : at<int32_t>(ws, L.idx);
@@ -785,7 +810,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
         if (hipEventRecord(side->fork, st) != hipSuccess ||
             hipStreamWaitEvent(side->s, side->fork, 0) != hipSuccess)
             return CLEARMOE_ERR_HIP;
-        rc = class_tokens_impl(s, *router, x, W1, b1, b2, z, false, y, L, ws, side->s);
+        rc = class_tokens_impl(s, *router, x, W1, b1, b2, z, false, y, L, ws, add_x, side->s);
         if (rc != CLEARMOE_OK) return rc;
         if (hipEventRecord(side->join, side->s) != hipSuccess) return CLEARMOE_ERR_HIP;
     }
@@ -819,6 +844,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
             c.stride = router->dense_stride;
             c.D = s.D;
             c.H = s.H;
+            c.add_x = add_x ? 1 : 0;
             class_ffn_plan(c, at<float>(ws, L.cpart), at<uint64_t>(ws, L.ccount));
         }
         CLEARMOE_STAGE(CLEARMOE_STAGE_FUSED_TOP1, st,
@@ -868,9 +894,10 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
         g.C = y; g.ldc = s.D; g.c_f32 = 0;
         g.c_rows = perm; g.c_div = 1;
         g.bias = b2;
+        g.res = skip; g.ldr = s.D;
         g.seg_offsets = offsets; g.nseg = s.E;
         CLEARMOE_STAGE(CLEARMOE_STAGE_Y, st, launch_gemm(s.dtype, g, st));
-        if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, true, y, L, ws, st);
+        if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, true, y, L, ws, add_x, st);
         return CLEARMOE_OK;
     }
 
@@ -957,6 +984,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
                 g.C = y; g.ldc = s.D; g.c_f32 = 0;
                 g.c_rows = pperm; g.c_div = 1;
                 g.bias = b2;
+                g.res = skip; g.ldr = s.D;
                 g.seg_offsets = poffsets; g.nseg = s.E;
                 CLEARMOE_STAGE(CLEARMOE_STAGE_Y, st, launch_gemm(s.dtype, g, st));
             }
@@ -986,11 +1014,12 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
         g.C = y; g.ldc = s.D; g.c_f32 = 0;
         g.c_rows = pperm; g.c_div = 1;
         g.bias = b2;
+        g.res = skip; g.ldr = s.D;
         g.seg_offsets = pair_seg; g.nseg = npairs;
         CLEARMOE_STAGE(CLEARMOE_STAGE_Y_PAIR, st, launch_gemm(s.dtype, g, st));
         // class tokens: their dense FFN output, from the token-order z when
         // there is one
-        if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, !z_pair_order, y, L, ws, st);
+        if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, !z_pair_order, y, L, ws, add_x, st);
         return CLEARMOE_OK;
     }
 
@@ -1004,7 +1033,7 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
     CLEARMOE_STAGE(CLEARMOE_STAGE_COMBINE_RES, st,
                    launch_combine_residual(s.dtype, hsh, hres, inv, y, T, s.D, s.k, A, st));
     // 7. class tokens: the dense FFN's output replaces theirs
-    if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, true, y, L, ws, st);
+    if (cls) return class_tokens_impl(s, *router, x, W1, b1, b2, z, true, y, L, ws, false, st);
     return CLEARMOE_OK;
 }
 
@@ -1335,7 +1364,7 @@ namespace {
 
 // The dense FFN y = GELU(x W1^T + b1) W2^T + b2 with z in the workspace.
 int dense_impl(const clearmoe_shape& s, const void* x, const void* W1, const float* b1,
-               const void* W2, const float* b2, void* y, void* z, hipStream_t st) {
+               const void* W2, const float* b2, void* y, void* z, bool add_x, hipStream_t st) {
     GemmDesc g = gemm_desc(s.T, s.H, s.D);
     g.A = x; g.lda = s.D;
     g.B = W1; g.ldb = s.D;
@@ -1347,6 +1376,9 @@ int dense_impl(const clearmoe_shape& s, const void* x, const void* W1, const flo
     g.B = W2; g.ldb = s.H;
     g.C = y; g.ldc = s.D; g.c_f32 = 0;
     g.bias = b2;
+    if (add_x) {
+        g.res = x; g.ldr = s.D;
+    }
     CLEARMOE_STAGE(CLEARMOE_STAGE_DENSE_FC2, st, launch_gemm(s.dtype, g, st));
     return CLEARMOE_OK;
 }
@@ -1428,16 +1460,19 @@ int clearmoe_stack_forward(const clearmoe_shape* shape, const clearmoe_stack_lay
         const clearmoe_stack_layer& L = layers[l];
         const clearmoe_shape sl = stack_layer_shape(s, L);
         void* out = l == n - 1 ? y : buf[l % 2];
-        void* f = residual ? F : out;
+        // the skip connection in the layer's last kernel, else in a pass of
+        // its own (6 us each at 12608 x 384)
+        const bool in_layer = residual && skip_in_layer(sl, L.moe ? &L.router : nullptr);
+        void* f = residual && !in_layer ? F : out;
         int rc;
         if (L.moe) {
             rc = ffn_forward_impl(&sl, &L.router, cur, L.W1, L.b1, L.US, L.Vt, L.b2, L.P, L.Q, f,
-                                  nullptr, nullptr, ws, most, stream);
+                                  nullptr, nullptr, ws, most, stream, nullptr, in_layer);
         } else {
-            rc = dense_impl(sl, cur, L.W1, L.b1, L.W2, L.b2, f, at<void>(ws, layout(sl).z), stream);
+            rc = dense_impl(sl, cur, L.W1, L.b1, L.W2, L.b2, f, at<void>(ws, layout(sl).z), in_layer, stream);
         }
         if (rc != CLEARMOE_OK) return rc;
-        if (residual)
+        if (residual && !in_layer)
             CLEARMOE_STAGE(CLEARMOE_STAGE_RESIDUAL_ADD, stream,
                            launch_residual_add(s.dtype, cur, F, out, s.T, s.D, stream));
         cur = out;

@@ -41,6 +41,8 @@ struct ClassArgs {
     int64_t ncls;          // class rows: ceil(T / stride)
     int64_t stride;        // tokens from one class row to the next
     int D, H;              // D <= 384 and H multiples of 8
+    int add_x;             // 1: y = round(x + round(f)), the skip connection (in the fused launch,
+                           //    of the tiles' rows too)
     int nparts;            // P: workgroups per 32-row block
     int per;               // chunks per part (the last part may take fewer, never none)
     float* part;           // P > 1: [blocks][P][32 x 384] float32 partial sums
@@ -244,7 +246,13 @@ __device__ __forceinline__ void class_ffn_block(const ClassArgs& c, int64_t j, u
             float v4[4];
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) v4[jj] = acc[t][4 * g + jj] + (c.b2 != nullptr ? c.b2[n + jj] : 0.0f);
-            *reinterpret_cast<uint2*>(yr + n) = make_uint2(pack2_bf16(v4[0], v4[1]), pack2_bf16(v4[2], v4[3]));
+            uint2 o = make_uint2(pack2_bf16(v4[0], v4[1]), pack2_bf16(v4[2], v4[3]));
+            if (c.add_x) {
+                const uint2 xv = *reinterpret_cast<const uint2*>(c.x + row * c.stride * D + n);
+                const u32x4 s = add8_bf16(u32x4{o.x, o.y, 0u, 0u}, u32x4{xv.x, xv.y, 0u, 0u});
+                o = make_uint2(s[0], s[1]);
+            }
+            *reinterpret_cast<uint2*>(yr + n) = o;
         }
     }
 }

@@ -261,6 +261,8 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 template <int NFT, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_fused_top1(FusedArgs a) {
+    // (no skip connection here: the branch alone cost 2 us of 62)
+    constexpr bool add_x = false;
 #include "fused_body.inc"
 }
 
@@ -276,6 +278,7 @@ void k_fused_top1_cls(FusedArgs a, ClassArgs c) {
         return;
     }
     constexpr bool SPLIT = false;
+    const bool add_x = c.add_x != 0;
 #include "fused_body.inc"
 }
 

@@ -589,8 +589,9 @@ static hipError_t gemm_dt(const GemmDesc& g, hipStream_t st) {
 }
 
 hipError_t launch_gemm(int dtype, const GemmDesc& g, hipStream_t st) {
+    if (dtype != 0 && gemm_bf16_supported(g)) return launch_gemm_bf16(g, st);
+    if (g.res != nullptr) return hipErrorInvalidValue;
     if (dtype == 0) return gemm_dt<float>(g, st);
-    if (gemm_bf16_supported(g)) return launch_gemm_bf16(g, st);
     return gemm_dt<bf16_bits>(g, st);
 }
 

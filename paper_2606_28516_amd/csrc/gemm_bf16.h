@@ -337,8 +337,12 @@ __device__ __forceinline__ void gb_epilogue(const GemmDesc& g, const GbTile& t, 
                     const int32_t cr = g.c_rows[cm];
                     cm = cr < 0 ? -1 : (g.c_div == 1 ? cr : cr / g.c_div);
                 }
-                if (cm >= 0)                            // a padding row is not stored
-                    gb_store(reinterpret_cast<u32x4*>(static_cast<bf16_bits*>(g.C) + cm * g.ldc + n), w, nt);
+                if (cm < 0) continue;                   // a padding row is not stored
+                u32x4 o = w;
+                if (EPI == kEpiPlain && g.res != nullptr)
+                    o = add8_bf16(o, *reinterpret_cast<const u32x4*>(static_cast<const bf16_bits*>(g.res) +
+                                                                     cm * g.ldr + n));
+                gb_store(reinterpret_cast<u32x4*>(static_cast<bf16_bits*>(g.C) + cm * g.ldc + n), o, nt);
             }
         }
         __builtin_amdgcn_wave_barrier();

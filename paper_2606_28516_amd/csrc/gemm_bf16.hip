@@ -107,6 +107,7 @@ bool gemm_bf16_supported(const GemmDesc& g) {
     if (g.row_scale != nullptr && (g.bias != nullptr || g.gelu || g.scale_col0 % 8 != 0 || g.scale_col1 % 8 != 0))
         return false;
     if (g.c_f32 && (g.gelu || g.row_scale != nullptr)) return false;
+    if (g.res != nullptr && (g.c_f32 || g.gelu || g.row_scale != nullptr || g.ldr % 8 != 0)) return false;
     return g.seg_offsets == nullptr || g.seg_merge || g.nseg <= 64;
 }
 

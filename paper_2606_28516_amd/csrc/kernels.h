@@ -61,6 +61,16 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Eight bf16 values plus eight others, rounded to bf16.
+__device__ __forceinline__ u32x4 add8_bf16(const u32x4& a, const u32x4& b) {
+    u32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        o[i] = pack2_bf16(__uint_as_float(a[i] << 16) + __uint_as_float(b[i] << 16),
+                          __uint_as_float(a[i] & 0xffff0000u) + __uint_as_float(b[i] & 0xffff0000u));
+    return o;
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static constexpr int per16 = 4;                 // elements per 16-byte piece
@@ -281,6 +291,9 @@ struct GemmDesc {
     int scale_col1;           //   (a negative scale row scales by 0)
     const float* row_scale2;
     int gelu;                 // 1: GELU after bias
+    const void* res;          // optional: res row added to each C row after rounding
+    int64_t ldr;              //   (C = round(round(epi) + res); row stride ldr; bfloat16 only,
+                              //   a shape for which gemm_bf16_supported holds)
     int64_t M;                // rows (sum of segments when grouped)
     int N, K;
     const int32_t* seg_offsets;  // optional [nseg+1] on the device: grouped GEMM
@@ -329,6 +342,7 @@ struct ClassArgs;
 // With cls (a planned class_ffn pass, class_ffn.h) the class rows' dense FFN
 // runs on extra workgroups of the same launch; only for a launch without
 // the hidden split (fused_split(T, E, H) == 1), else an invalid-value error.
+// Its add_x asks for the skip connection in every row of y.
 hipError_t launch_fused_top1(const void* x, const void* W1, const float* b1, const void* US,
                              const void* Vt, const float* b2, const void* P, const void* Q,
                              const int32_t* perm, const int32_t* offsets, const int32_t* idx,
