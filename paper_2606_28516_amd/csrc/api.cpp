@@ -387,12 +387,13 @@ int check_router(const clearmoe_shape& s, const clearmoe_router* r, size_t wa = 
 
 // Routing and the per-tile histogram (left in the workspace for dispatch).
 int route_impl(const clearmoe_shape& s, const Layout& L, const clearmoe_router& rt, const void* x,
-               int32_t* idx, float* gate, void* ws, hipStream_t st) {
+               int32_t* idx, float* gate, void* ws, hipStream_t st, int32_t* zero = nullptr,
+               int nzero = 0) {
     int32_t* tc = at<int32_t>(ws, L.tile_counts);
     if (rt.hidden == 0) {
         CLEARMOE_STAGE(CLEARMOE_STAGE_ROUTE, st,
                        launch_route(s.dtype, x, rt.Wg, rt.bg, s.T, s.D, s.E, s.k, rt.adaptive,
-                                    s.renorm, rt.tau, rt.dense_stride, idx, gate, tc, st));
+                                    s.renorm, rt.tau, rt.dense_stride, idx, gate, tc, zero, nzero, st));
         return CLEARMOE_OK;
     }
     CLEARMOE_STAGE(CLEARMOE_STAGE_ROUTE, st,
@@ -400,7 +401,7 @@ int route_impl(const clearmoe_shape& s, const Layout& L, const clearmoe_router& 
                                     s.E, s.k, rt.adaptive, s.renorm, rt.tau, rt.dense_stride,
                                     idx, gate, st));
     CLEARMOE_STAGE(CLEARMOE_STAGE_TILE_HIST, st,
-                   launch_tile_histogram(idx, s.T, s.E, s.k, tc, st));
+                   launch_tile_histogram(idx, s.T, s.E, s.k, tc, zero, nzero, st));
     return CLEARMOE_OK;
 }
 
@@ -423,7 +424,7 @@ int dispatch_impl(const clearmoe_shape& s, const Layout& L, const int32_t* idx, 
     const int64_t nt = route_tiles(s.T);
     if (!hist_in_ws)
         CLEARMOE_STAGE(CLEARMOE_STAGE_TILE_HIST, st,
-                       launch_tile_histogram(idx, s.T, s.E, s.k, tc, st));
+                       launch_tile_histogram(idx, s.T, s.E, s.k, tc, nullptr, 0, st));
     if (hist_tiles(s.T, s.E) * s.E <= kInlineScanMax) {
         // small histogram: the permutation scans it itself (one launch fewer)
         CLEARMOE_STAGE(CLEARMOE_STAGE_PERMUTE, st,
@@ -818,7 +819,14 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
     // (the fused top-1 kernel does the latter itself from the histogram
     // when it is small enough for one workgroup's scan; the pair order
     // dispatches pair keys instead, below)
-    rc = route_impl(s, L, *router, x, idx, gate, ws, st);
+    // the router also clears the counters that the fused kernel's hidden split
+    // or the grouped products' split K will count arrivals in
+    const bool top1_rows = s.k == 1 || (router->adaptive && pair_path(s));
+    const bool fused_rows = s.dtype == CLEARMOE_BF16 && fused_top1_supported(s.D, s.H, s.r, s.q);
+    const int nzero = !top1_rows ? 0
+                      : !fused_rows ? kGemmKsplitTiles
+                      : fused_split(T, s.E, s.H) > 1 ? static_cast<int>(fused_counters(T, s.E)) : 0;
+    rc = route_impl(s, L, *router, x, idx, gate, ws, st, at<int32_t>(ws, L.fcount), nzero);
     if (rc != CLEARMOE_OK) return rc;
     // (the fused kernel's own dispatch takes every top-1 gate as 1, which
     // holds for renormalised gates only; with renorm == 0 it reads them

@@ -40,7 +40,8 @@ __device__ __forceinline__ int wave_rank(bool ok, int ex, int E, int lane, int w
 template <int TILE>
 __global__ __launch_bounds__(TILE) void k_tile_hist(const int32_t* __restrict__ idx, int64_t T,
                                                      int E, int k,
-                                                     int32_t* __restrict__ tile_counts) {
+                                                     int32_t* __restrict__ tile_counts,
+                                                     int32_t* __restrict__ zero, int nzero) {
     constexpr int kW = TILE / 64;
     __shared__ int s_wc[kW][64];
     __shared__ int s_run[64];
@@ -49,6 +50,7 @@ __global__ __launch_bounds__(TILE) void k_tile_hist(const int32_t* __restrict__ 
     const int64_t a0 = static_cast<int64_t>(blockIdx.x) * TILE * k;
     const int64_t na64 = A - a0 < static_cast<int64_t>(TILE) * k ? A - a0 : static_cast<int64_t>(TILE) * k;
     const int na = static_cast<int>(na64);
+    for (int i = blockIdx.x * TILE + tid; i < nzero; i += gridDim.x * TILE) zero[i] = 0;
     if (tid < E) s_run[tid] = 0;
     __syncthreads();
     for (int c = 0; c < k; ++c) {
@@ -395,15 +397,15 @@ __global__ __launch_bounds__(256) void k_combine_residual(const float* __restric
 }
 
 hipError_t launch_tile_histogram(const int32_t* idx, int64_t T, int E, int k,
-                                 int32_t* tile_counts, hipStream_t st) {
+                                 int32_t* tile_counts, int32_t* zero, int nzero, hipStream_t st) {
     const int64_t nt = hist_tiles(T, E);
     if (nt == 0) return hipSuccess;
     if (hist_tile(T, E) == kSmallTile)
         launch_kernel(k_tile_hist<kSmallTile>, dim3(static_cast<unsigned>(nt)), kSmallTile, 0, st, idx, T, E, k,
-                                                                                        tile_counts);
+                                                                                        tile_counts, zero, nzero);
     else
         launch_kernel(k_tile_hist<kRouteTile>, dim3(static_cast<unsigned>(nt)), kRouteTile, 0, st, idx, T, E, k,
-                                                                                        tile_counts);
+                                                                                        tile_counts, zero, nzero);
     return hipGetLastError();
 }
 

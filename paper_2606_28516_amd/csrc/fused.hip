@@ -55,13 +55,6 @@ FusedLds fused_lds(int D, int H, int r, int q) {
 
 }  // namespace
 
-// Arrival counters of the hidden split start at zero in every launch (a fill
-// kernel, so that the launch sequence records no memset).
-__global__ void k_zero_counters(int32_t* c, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) c[i] = 0;
-}
-
 int fused_split(int64_t T, int E, int H) {
     const int64_t tiles = (T + kFRows - 1) / kFRows + E;
     const int64_t groups = (H + 4 * kFHid - 1) / (4 * kFHid);   // four-slice groups
@@ -150,18 +143,6 @@ hipError_t launch_fused_top1(const void* x, const void* W1, const float* b1, con
     per_xcd = (per_xcd + split - 1) / split * split;
     a.per_xcd = per_xcd;
     const int grid = a.per_xcd * kFXcds;
-    if (split > 1) {
-        // the fill kernel must not take the timing events meant for the
-        // fused launch
-        LaunchTiming& lt = launch_timing();
-        const LaunchTiming keep = lt;
-        lt = LaunchTiming{};
-        launch_kernel(k_zero_counters, dim3((a.tiles_bound + 255) / 256), 256, 0, st, counters,
-                      a.tiles_bound);
-        lt = keep;
-        const hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-    }
     if (split > 1) return fused_launch_split(a, lds, grid, nft, st);
     if (cls != nullptr && cls->ncls > 0) {
         // the class rows' workgroups after the tiles' (their LDS plan is far

@@ -364,19 +364,20 @@ void k_gemm(GemmDesc g, int mtiles, int ntiles, int group, int ksplit, int stage
                                      acc[i][j][4 * q + 3]};
                     __builtin_amdgcn_raw_buffer_store_b128(v, rp, off(kp, i, j, q), 0, kDevScope);
                 }
-        // release: every wave's partial stores have completed (vmcnt) and the
-        // barrier orders them before thread 0's agent-scope release add; the
-        // part that sees the count complete acquires at agent scope before
-        // any wave reads the partials
+        // every wave's partial stores, device scope (they miss the L1 and are
+        // coherent across the L2s, as relaxed device-scope atomics are), have
+        // completed (vmcnt), and the barrier orders them before thread 0's
+        // add; the part that sees the count complete issues its device-scope
+        // loads after it.  No plain access is part of this, so the add needs
+        // no release or acquire, which would write back and invalidate the L2.
         wait_vmcnt<0>();
         __syncthreads();
         __shared__ int s_last;
         if (tid == 0)
-            s_last = __hip_atomic_fetch_add(g.ks_count + tile, 1, __ATOMIC_ACQ_REL,
+            s_last = __hip_atomic_fetch_add(g.ks_count + tile, 1, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT) == S - 1;
         __syncthreads();
         if (!s_last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -508,11 +509,6 @@ void k_gemm(GemmDesc g, int mtiles, int ntiles, int group, int ksplit, int stage
     }
 }
 
-__global__ void k_zero_tiles(int32_t* c, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) c[i] = 0;
-}
-
 // Split K (S parts of every tile's k stages) when the tiles alone would leave
 // most CUs idle and every part still has four stages or more.
 int gemm_ksplit(int64_t tiles, int nk) {
@@ -546,17 +542,6 @@ static hipError_t gemm_cfg(const GemmDesc& g, hipStream_t st) {
     // and costs for short K (fc1 +1 %, DeiT-Small fc1 +5 %)
     const int group = 4, staged = g.K >= 2048 ? 1 : 0;
     const int64_t grid = per_xcd * kXcds;
-    if (S > 1) {
-        // the fill kernel must not take the timing events meant for the GEMM
-        LaunchTiming& lt = launch_timing();
-        const LaunchTiming keep = lt;
-        lt = LaunchTiming{};
-        launch_kernel(k_zero_tiles, dim3(1), kGemmKsplitTiles, 0, st, d.ks_count,
-                      static_cast<int>(tiles));
-        lt = keep;
-        const hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-    }
     launch_kernel(k_gemm<Tin, BM, BN, WM, WN, NS, SB, WPE>, dim3(static_cast<unsigned>(grid)), 64 * WM * WN, 0, st,
         d, static_cast<int>(mt), static_cast<int>(nt), group, S, staged);
     return hipGetLastError();

@@ -160,11 +160,14 @@ __host__ __device__ inline int64_t hist_tiles(int64_t T, int E) {
 // ---------------------------------------------------------------------------
 // Router logits (float32 MFMA, certified; double recompute of near ties),
 // top-k (adaptive != 0: top-1 / top-2 by confidence tau, k = 2 slots), gates,
-// per-tile expert histogram (tile_counts may be NULL).  dense_stride > 0:
+// per-tile expert histogram (tile_counts may be NULL); sets nzero words at
+// zero to 0 (counters of later kernels of the stream; a fill of their own costs
+// a launch, 4 us).  dense_stride > 0:
 // tokens t with t % dense_stride == 0 get no expert (all slots -1, gate 0).
 hipError_t launch_route(int dtype, const void* x, const void* Wg, const float* bg, int64_t T,
                         int D, int E, int k, int adaptive, int renorm, double tau, int dense_stride,
-                        int32_t* idx, float* gate, int32_t* tile_counts, hipStream_t st);
+                        int32_t* idx, float* gate, int32_t* tile_counts, int32_t* zero, int nzero,
+                        hipStream_t st);
 // MLP router: hidden GELU(x Wh^T + bh) of width Hr (1..kMlpHiddenMax) rounded
 // to the storage type, logits hr Wo^T + bo in double; then as launch_route
 // (no histogram).
@@ -173,9 +176,10 @@ hipError_t launch_route_mlp(int dtype, const void* x, const void* Wh, const floa
                             int k, int adaptive, int renorm, double tau, int dense_stride, int32_t* idx,
                             float* gate, hipStream_t st);
 constexpr int kMlpHiddenMax = 256;
-// Per-tile expert histogram of an index array (tiles of hist_tile(T, E) tokens).
+// Per-tile expert histogram of an index array (tiles of hist_tile(T, E)
+// tokens); zero and nzero as launch_route's.
 hipError_t launch_tile_histogram(const int32_t* idx, int64_t T, int E, int k,
-                                 int32_t* tile_counts, hipStream_t st);
+                                 int32_t* tile_counts, int32_t* zero, int nzero, hipStream_t st);
 // Chunked exclusive scan of 256-token tile histograms: for tile b in chunk
 // c = b / 256, tile_base[b][e] = sum of tile_counts[b'][e] over the earlier
 // tiles b' of chunk c, and chunk_tot[c][e] = the chunk's column sums
@@ -300,7 +304,8 @@ struct GemmDesc {
     int nseg;
     // optional split K for products with few tiles and long K (see
     // gemm_ksplit): float32 partial tiles (kGemmKsplitBytes) and per-tile
-    // arrival counters (kGemmKsplitTiles int32) of workspace
+    // arrival counters (kGemmKsplitTiles int32, zero before the launch) of
+    // workspace
     float* ks_part;
     int32_t* ks_count;
 };
@@ -351,9 +356,11 @@ hipError_t launch_fused_top1(const void* x, const void* W1, const float* b1, con
                              hipStream_t st, const ClassArgs* cls = nullptr);
 // Small batches (fewer 64-row tiles than CUs) split each tile's hidden units
 // over fused_split(T, E, H) workgroups; the launch then needs part
-// (fused_part_bytes) and counters (T / 64 + E + 1 int32) of workspace, else
+// (fused_part_bytes) and counters (fused_counters int32, zero before
+// the launch) of workspace, else
 // both may be NULL.
 int fused_split(int64_t T, int E, int H);
+inline int64_t fused_counters(int64_t T, int E) { return (T + 63) / 64 + E; }   // one per tile
 size_t fused_part_bytes(int64_t T, int E, int H, int r, int q);
 
 }  // namespace clearmoe

@@ -210,14 +210,21 @@ typedef __attribute__((address_space(3))) uint32_t route_lds_word;
 
 // w_lds > 0: the router matrix (E x D, w_lds bytes of dynamic LDS) is copied to
 // LDS for the exact recompute of uncertified tokens.
-template <typename Tin, int EG, int NB, int KP>
+// EP: experts a lane chooses from after the transpose, 16 EG or, for E <= 8, 8
+// (the choice is vector work in double on every token: with 16 slots it took
+// half of the kernel's instructions at E = 8).  nzero words at zero are set to
+// 0: the arrival counters of the layer's later kernels.
+template <typename Tin, int EG, int NB, int KP, int EP = 16 * EG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EG == 1 ? 2 : 1)))
 void k_route(
     const Tin* __restrict__ x, const Tin* __restrict__ Wg, const float* __restrict__ bg, int64_t T,
     int D, int E, int k, int adaptive, int renorm, double tau, int dense_stride, int32_t* __restrict__ idx,
-    float* __restrict__ gate, int32_t* __restrict__ tile_counts, int w_lds) {
+    float* __restrict__ gate, int32_t* __restrict__ tile_counts, int w_lds, int32_t* __restrict__ zero,
+    int nzero) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_w[];
-    constexpr int EP = 16 * EG;                      // experts padded to MFMA rows
+    constexpr int EL = EP < 16 ? EP : 16;            // of them in one 16-row MFMA group
+    constexpr int kPitch = EL + 1;
+    static_assert(EP == 16 * EG || (EG == 1 && EP == 8), "experts padded to MFMA rows, or eight");
     constexpr int PER16 = Elem<Tin>::per16;
     constexpr int KS = RouteMfma<Tin>::kstep;
     constexpr int kPart = RouteMfma<Tin>::kpart;
@@ -225,7 +232,7 @@ void k_route(
     constexpr int kTok = 16 * NB;                    // tokens per wave
     constexpr int kTile = kWaves * kTok;             // tokens per workgroup = histogram tile
     static_assert(kTile == kRouteTile || kTile == kSmallTile, "histogram tile sizes");
-    __shared__ double s_l[kWaves][64][17];           // kTok rows; 64 for the recompute's sums
+    __shared__ double s_l[kWaves][64][kPitch];       // kTok rows; 64 for the recompute's sums
     __shared__ float s_s[kWaves][kTok][4 * EG + 1];
     __shared__ int s_wcnt[kWaves][64];
     __shared__ double s_fb[kWaves][4][EP];           // recomputed logits of a batch
@@ -240,6 +247,7 @@ void k_route(
     const __amdgpu_buffer_rsrc_t rx = raw_rsrc(x + tile0 * D, static_cast<int64_t>(rows) * D * esz);
     const __amdgpu_buffer_rsrc_t rw = raw_rsrc(Wg, static_cast<int64_t>(E) * D * esz);
     __shared__ double bgv[EP];                       // router bias, loaded up front (read
+    for (int i = blockIdx.x * 256 + tid; i < nzero; i += gridDim.x * 256) zero[i] = 0;
     if (tid < EP)                                    // after the barrier past the transposes)
         bgv[tid] = (bg != nullptr && tid < E) ? static_cast<double>(bg[tid]) : 0.0;
 
@@ -350,7 +358,8 @@ void k_route(
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s_l[w][16 * b + col][4 * grp + v] = lacc[g][b][v];
+            for (int v = 0; v < 4; ++v)
+                if (EL == 16 || grp < 2) s_l[w][16 * b + col][4 * grp + v] = lacc[g][b][v];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             float m = 0.0f;
@@ -364,7 +373,7 @@ void k_route(
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lg[16 * g + e] = s_l[w][tl][e];
+        for (int e = 0; e < EL; ++e) lg[16 * g + e] = s_l[w][tl][e];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -448,12 +457,12 @@ void k_route(
         }
         // sums over each group's G lanes through LDS (this wave's transpose
         // rows, free by now): lane (q, e) adds its group's column e
-        double* red = &s_l[w][0][0];                  // [64 lanes][16 experts], pitch 17
+        double* red = &s_l[w][0][0];                  // [64 lanes][EL experts], pitch kPitch
 #pragma unroll
         for (int g = 0; g < EG; ++g) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (16 * g + e < E) red[lane * 17 + e] = part[16 * g + e];
+            for (int e = 0; e < EL; ++e)
+                if (16 * g + e < E) red[lane * kPitch + e] = part[16 * g + e];
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -461,7 +470,7 @@ void k_route(
                 const int qq = lane >> 4, e = lane & 15;
                 if (16 * g + e < E) {
                     double acc = 0.0;
-                    for (int j = 0; j < G; ++j) acc += red[(qq * G + j) * 17 + e];
+                    for (int j = 0; j < G; ++j) acc += red[(qq * G + j) * kPitch + e];
                     s_fb[w][qq][16 * g + e] = acc;
                 }
             }
@@ -676,7 +685,7 @@ constexpr int64_t kRouteWLds = 32 * 1024;
 template <typename Tin>
 static hipError_t route_dt(const Tin* x, const Tin* Wg, const float* bg, int64_t T, int D, int E,
                            int k, int adaptive, int renorm, double tau, int dense_stride, int32_t* idx,
-                           float* gate, int32_t* tc, hipStream_t st) {
+                           float* gate, int32_t* tc, int32_t* zero, int nzero, hipStream_t st) {
     const int64_t blocks = hist_tiles(T, E);
     if (blocks == 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(blocks));
@@ -684,33 +693,30 @@ static hipError_t route_dt(const Tin* x, const Tin* Wg, const float* bg, int64_t
     // the router rows go to LDS when they fit in kRouteWLds (whole 1 KB rounds)
     const int64_t wbytes = static_cast<int64_t>(E) * D * static_cast<int64_t>(sizeof(Tin));
     const int w_lds = wbytes <= kRouteWLds ? static_cast<int>((wbytes + 1023) / 1024 * 1024) : 0;
-    if (small)
-        launch_kernel(k_route<Tin, 1, 1, 12>, grid, 256, w_lds, st, x, Wg, bg, T, D, E, k, adaptive, renorm, tau,
-                                                          dense_stride, idx, gate, tc, w_lds);
-    else if (E <= 16)
-        launch_kernel(k_route<Tin, 1, 4, KPRE>, grid, kRouteTile, w_lds, st, x, Wg, bg, T, D, E, k, adaptive,
-                                                                   renorm, tau, dense_stride, idx, gate, tc,
-                                                                   w_lds);
-    else if (E <= 32)
-        launch_kernel(k_route<Tin, 2, 4, KPRE>, grid, kRouteTile, w_lds, st, x, Wg, bg, T, D, E, k, adaptive,
-                                                                   renorm, tau, dense_stride, idx, gate, tc,
-                                                                   w_lds);
-    else
-        launch_kernel(k_route<Tin, 4, 4, KPRE>, grid, kRouteTile, w_lds, st, x, Wg, bg, T, D, E, k, adaptive,
-                                                                   renorm, tau, dense_stride, idx, gate, tc,
-                                                                   w_lds);
+    auto go = [&](auto* kernel) {
+        launch_kernel(kernel, grid, 256, w_lds, st, x, Wg, bg, T, D, E, k, adaptive, renorm, tau, dense_stride,
+                      idx, gate, tc, w_lds, zero, nzero);
+    };
+    if (small && E <= 8) go(&k_route<Tin, 1, 1, 12, 8>);
+    else if (small) go(&k_route<Tin, 1, 1, 12>);
+    else if (E <= 8) go(&k_route<Tin, 1, 4, KPRE, 8>);
+    else if (E <= 16) go(&k_route<Tin, 1, 4, KPRE>);
+    else if (E <= 32) go(&k_route<Tin, 2, 4, KPRE>);
+    else go(&k_route<Tin, 4, 4, KPRE>);
     return hipGetLastError();
 }
 
 hipError_t launch_route(int dtype, const void* x, const void* Wg, const float* bg, int64_t T,
                         int D, int E, int k, int adaptive, int renorm, double tau, int dense_stride,
-                        int32_t* idx, float* gate, int32_t* tile_counts, hipStream_t st) {
+                        int32_t* idx, float* gate, int32_t* tile_counts, int32_t* zero, int nzero,
+                        hipStream_t st) {
     if (dtype == 0)
         return route_dt<float>(static_cast<const float*>(x), static_cast<const float*>(Wg), bg, T,
-                               D, E, k, adaptive, renorm, tau, dense_stride, idx, gate, tile_counts, st);
+                               D, E, k, adaptive, renorm, tau, dense_stride, idx, gate, tile_counts, zero, nzero,
+                               st);
     return route_dt<bf16_bits>(static_cast<const bf16_bits*>(x), static_cast<const bf16_bits*>(Wg),
                                bg, T, D, E, k, adaptive, renorm, tau, dense_stride, idx, gate, tile_counts,
-                               st);
+                               zero, nzero, st);
 }
 
 }  // namespace clearmoe
