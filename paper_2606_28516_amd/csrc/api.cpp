@@ -1053,11 +1053,11 @@ namespace {
 // [batches][prow][pcol] with zeros around; a NULL src (an operand the path
 // does not read) stays NULL.
 int pad_operand(int eb, const void* src, void* ws, size_t off, int64_t batches, int64_t rows,
-                int64_t cols, int64_t prow, int64_t pcol, hipStream_t st, const void** out) {
+                int64_t cols, int64_t prow, int64_t pcol, PadJobs& jobs, const void** out) {
     *out = nullptr;
     if (src == nullptr) return CLEARMOE_OK;
     void* dst = at<void>(ws, off);
-    if (launch_pad_copy(eb, src, dst, batches, rows, cols, prow, pcol, st) != hipSuccess)
+    if (pad_jobs_add(jobs, eb, src, dst, batches, rows, cols, prow, pcol) != hipSuccess)
         return CLEARMOE_ERR_HIP;
     *out = dst;
     return CLEARMOE_OK;
@@ -1090,21 +1090,23 @@ int ffn_forward_unaligned(const clearmoe_shape& s, const clearmoe_router* router
     const int eb = static_cast<int>(es);
     const int64_t T = s.T, E = s.E;
     const void *xp, *W1p, *b1p, *USp, *Vtp, *b2p, *Pp, *Qp;
-    int rc = pad_operand(eb, x, ws, pl.x, 1, T, s.D, T, a.D, st, &xp);
-    if (rc == CLEARMOE_OK) rc = pad_operand(eb, W1, ws, pl.W1, 1, s.H, s.D, a.H, a.D, st, &W1p);
-    if (rc == CLEARMOE_OK) rc = pad_operand(4, b1, ws, pl.b1, 1, 1, s.H, 1, a.H, st, &b1p);
-    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.r > 0 ? US : nullptr, ws, pl.US, 1, s.D, s.r, a.D, a.r, st, &USp);
-    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.r > 0 ? Vt : nullptr, ws, pl.Vt, 1, s.r, s.H, a.r, a.H, st, &Vtp);
-    if (rc == CLEARMOE_OK) rc = pad_operand(4, b2, ws, pl.b2, 1, 1, s.D, 1, a.D, st, &b2p);
-    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.q > 0 ? P : nullptr, ws, pl.P, E, s.D, s.q, a.D, a.q, st, &Pp);
-    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.q > 0 ? Q : nullptr, ws, pl.Q, E, s.q, s.H, a.q, a.H, st, &Qp);
+    PadJobs jobs{};
+    int rc = pad_operand(eb, x, ws, pl.x, 1, T, s.D, T, a.D, jobs, &xp);
+    if (rc == CLEARMOE_OK) rc = pad_operand(eb, W1, ws, pl.W1, 1, s.H, s.D, a.H, a.D, jobs, &W1p);
+    if (rc == CLEARMOE_OK) rc = pad_operand(4, b1, ws, pl.b1, 1, 1, s.H, 1, a.H, jobs, &b1p);
+    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.r > 0 ? US : nullptr, ws, pl.US, 1, s.D, s.r, a.D, a.r, jobs, &USp);
+    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.r > 0 ? Vt : nullptr, ws, pl.Vt, 1, s.r, s.H, a.r, a.H, jobs, &Vtp);
+    if (rc == CLEARMOE_OK) rc = pad_operand(4, b2, ws, pl.b2, 1, 1, s.D, 1, a.D, jobs, &b2p);
+    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.q > 0 ? P : nullptr, ws, pl.P, E, s.D, s.q, a.D, a.q, jobs, &Pp);
+    if (rc == CLEARMOE_OK) rc = pad_operand(eb, s.q > 0 ? Q : nullptr, ws, pl.Q, E, s.q, s.H, a.q, a.H, jobs, &Qp);
     clearmoe_router rt = *router;
     if (rc == CLEARMOE_OK && rt.hidden == 0)   // linear router: Wg [E, D]
-        rc = pad_operand(eb, router->Wg, ws, pl.Wg, 1, E, s.D, E, a.D, st, &rt.Wg);
+        rc = pad_operand(eb, router->Wg, ws, pl.Wg, 1, E, s.D, E, a.D, jobs, &rt.Wg);
     if (rc == CLEARMOE_OK && rt.hidden > 0)    // MLP router: Wh [hidden, D] (Wg is [E, hidden])
-        rc = pad_operand(eb, router->Wh, ws, pl.Wh, 1, rt.hidden, s.D, rt.hidden, a.D, st, &rt.Wh);
+        rc = pad_operand(eb, router->Wh, ws, pl.Wh, 1, rt.hidden, s.D, rt.hidden, a.D, jobs, &rt.Wh);
     if (rc == CLEARMOE_OK && rt.W2 != nullptr)  // class tokens' fc2 [D, H]
-        rc = pad_operand(eb, router->W2, ws, pl.W2, 1, s.D, s.H, a.D, a.H, st, &rt.W2);
+        rc = pad_operand(eb, router->W2, ws, pl.W2, 1, s.D, s.H, a.D, a.H, jobs, &rt.W2);
+    if (rc == CLEARMOE_OK && launch_pad_jobs(jobs, st) != hipSuccess) rc = CLEARMOE_ERR_HIP;
     if (rc != CLEARMOE_OK) return rc;
     void* yp = at<void>(ws, pl.y);
     rc = ffn_forward_impl(&a, &rt, xp, W1p, static_cast<const float*>(b1p), USp, Vtp,
@@ -1128,12 +1130,14 @@ int route_unaligned(const clearmoe_shape& s, const clearmoe_router& router, cons
     const int eb = static_cast<int>(es);
     const int64_t T = s.T, E = s.E;
     const void* xp;
-    int rc = pad_operand(eb, x, ws, rp.x, 1, T, s.D, T, rp.a.D, st, &xp);
+    PadJobs jobs{};
+    int rc = pad_operand(eb, x, ws, rp.x, 1, T, s.D, T, rp.a.D, jobs, &xp);
     clearmoe_router rt = router;
     if (rc == CLEARMOE_OK && rt.hidden == 0)   // linear router: Wg [E, D]
-        rc = pad_operand(eb, router.Wg, ws, rp.Wg, 1, E, s.D, E, rp.a.D, st, &rt.Wg);
+        rc = pad_operand(eb, router.Wg, ws, rp.Wg, 1, E, s.D, E, rp.a.D, jobs, &rt.Wg);
     if (rc == CLEARMOE_OK && rt.hidden > 0)    // MLP router: Wh [hidden, D] (Wg is [E, hidden])
-        rc = pad_operand(eb, router.Wh, ws, rp.Wh, 1, rt.hidden, s.D, rt.hidden, rp.a.D, st, &rt.Wh);
+        rc = pad_operand(eb, router.Wh, ws, rp.Wh, 1, rt.hidden, s.D, rt.hidden, rp.a.D, jobs, &rt.Wh);
+    if (rc == CLEARMOE_OK && launch_pad_jobs(jobs, st) != hipSuccess) rc = CLEARMOE_ERR_HIP;
     if (rc != CLEARMOE_OK) return rc;
     return route_impl(rp.a, layout(rp.a), rt, xp, idx, gate, ws, st);
 }
@@ -1322,11 +1326,13 @@ int clearmoe_dense_ffn_forward(const clearmoe_shape* shape, const void* x, const
         const clearmoe_shape a = aligned_shape(s);
         const int eb = static_cast<int>(es);
         const void *xp, *W1p, *b1p, *W2p, *b2p;
-        int rc = pad_operand(eb, x, ws, pl.x, 1, s.T, s.D, s.T, a.D, stream, &xp);
-        if (rc == CLEARMOE_OK) rc = pad_operand(eb, W1, ws, pl.W1, 1, s.H, s.D, a.H, a.D, stream, &W1p);
-        if (rc == CLEARMOE_OK) rc = pad_operand(4, b1, ws, pl.b1, 1, 1, s.H, 1, a.H, stream, &b1p);
-        if (rc == CLEARMOE_OK) rc = pad_operand(eb, W2, ws, pl.W2, 1, s.D, s.H, a.D, a.H, stream, &W2p);
-        if (rc == CLEARMOE_OK) rc = pad_operand(4, b2, ws, pl.b2, 1, 1, s.D, 1, a.D, stream, &b2p);
+        PadJobs jobs{};
+        int rc = pad_operand(eb, x, ws, pl.x, 1, s.T, s.D, s.T, a.D, jobs, &xp);
+        if (rc == CLEARMOE_OK) rc = pad_operand(eb, W1, ws, pl.W1, 1, s.H, s.D, a.H, a.D, jobs, &W1p);
+        if (rc == CLEARMOE_OK) rc = pad_operand(4, b1, ws, pl.b1, 1, 1, s.H, 1, a.H, jobs, &b1p);
+        if (rc == CLEARMOE_OK) rc = pad_operand(eb, W2, ws, pl.W2, 1, s.D, s.H, a.D, a.H, jobs, &W2p);
+        if (rc == CLEARMOE_OK) rc = pad_operand(4, b2, ws, pl.b2, 1, 1, s.D, 1, a.D, jobs, &b2p);
+        if (rc == CLEARMOE_OK && launch_pad_jobs(jobs, stream) != hipSuccess) rc = CLEARMOE_ERR_HIP;
         if (rc != CLEARMOE_OK) return rc;
         void* yp = at<void>(ws, pl.y);
         rc = clearmoe_dense_ffn_forward(&a, xp, W1p, static_cast<const float*>(b1p), W2p,

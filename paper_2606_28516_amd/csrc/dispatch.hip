@@ -584,36 +584,68 @@ hipError_t launch_residual_add(int dtype, const void* x, const void* f, void* ou
     return hipGetLastError();
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_pad_copy(const T* __restrict__ src, T* __restrict__ dst,
-                                                  int64_t batches, int64_t srows, int64_t scols,
-                                                  int64_t drows, int64_t dcols) {
-    const int64_t n = batches * drows * dcols;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int64_t c = i % dcols, br = i / dcols;
-        const int64_t r = br % drows, b = br / drows;
-        dst[i] = (r < srows && c < scols) ? src[(b * srows + r) * scols + c] : T(0);
+// Elements block * 256 + tid, + blocks * 256, ... of one copy; I: the index
+// type (32 bits where the destination allows: the two divisions an element
+// are most of the work).
+template <typename T, typename I>
+__device__ __forceinline__ void pad_elems(const PadJob& j, int block) {
+    const T* src = static_cast<const T*>(j.src);
+    T* dst = static_cast<T*>(j.dst);
+    const I n = static_cast<I>(j.batches * j.drows * j.dcols), dcols = static_cast<I>(j.dcols),
+            drows = static_cast<I>(j.drows), srows = static_cast<I>(j.srows), scols = static_cast<I>(j.scols);
+    const I step = static_cast<I>(j.blocks) * 256;
+    for (I i = static_cast<I>(block) * 256 + threadIdx.x; i < n; i += step) {
+        const I br = i / dcols, c = i - br * dcols, b = br / drows, r = br - b * drows;
+        dst[i] = (r < srows && c < scols)
+                     ? src[(static_cast<int64_t>(b) * j.srows + r) * j.scols + c] : T(0);
     }
+}
+
+// Workgroups [0, blocks) take the first copy, the next ones the second, ...
+__global__ __launch_bounds__(256) void k_pad_jobs(PadJobs p) {
+    int block = blockIdx.x, k = 0;
+    while (k + 1 < p.n && block >= p.job[k].blocks) {
+        block -= p.job[k].blocks;
+        ++k;
+    }
+    const PadJob& j = p.job[k];
+    // i + step must not wrap in 32 bits: step is at most 8192 * 256
+    const bool narrow = j.batches * j.drows * j.dcols < (int64_t{1} << 31);
+    if (j.elem_bytes == 4) {
+        if (narrow) pad_elems<uint32_t, uint32_t>(j, block);
+        else pad_elems<uint32_t, int64_t>(j, block);
+    } else {
+        if (narrow) pad_elems<uint16_t, uint32_t>(j, block);
+        else pad_elems<uint16_t, int64_t>(j, block);
+    }
+}
+
+hipError_t pad_jobs_add(PadJobs& jobs, int elem_bytes, const void* src, void* dst, int64_t batches,
+                        int64_t srows, int64_t scols, int64_t drows, int64_t dcols) {
+    if (batches < 0 || srows < 0 || scols < 0 || drows < 0 || dcols < 0) return hipErrorInvalidValue;
+    const int64_t n = batches * drows * dcols;
+    if (n == 0) return hipSuccess;
+    if (src == nullptr || dst == nullptr || (elem_bytes != 2 && elem_bytes != 4) || jobs.n >= kPadJobs)
+        return hipErrorInvalidValue;
+    const int64_t b = (n + 255) / 256;
+    jobs.job[jobs.n++] = PadJob{src, dst, batches, srows, scols, drows, dcols, elem_bytes,
+                                static_cast<int>(b < 8192 ? b : 8192)};
+    return hipSuccess;
+}
+
+hipError_t launch_pad_jobs(const PadJobs& jobs, hipStream_t st) {
+    int blocks = 0;
+    for (int i = 0; i < jobs.n; ++i) blocks += jobs.job[i].blocks;
+    if (blocks == 0) return hipSuccess;
+    launch_kernel(k_pad_jobs, dim3(static_cast<unsigned>(blocks)), 256, 0, st, jobs);
+    return hipGetLastError();
 }
 
 hipError_t launch_pad_copy(int elem_bytes, const void* src, void* dst, int64_t batches, int64_t srows,
                            int64_t scols, int64_t drows, int64_t dcols, hipStream_t st) {
-    if (batches < 0 || srows < 0 || scols < 0 || drows < 0 || dcols < 0) return hipErrorInvalidValue;
-    const int64_t n = batches * drows * dcols;
-    if (n == 0) return hipSuccess;
-    if (src == nullptr || dst == nullptr) return hipErrorInvalidValue;
-    const int64_t b = (n + 255) / 256;
-    const unsigned blocks = static_cast<unsigned>(b < 8192 ? b : 8192);
-    if (elem_bytes == 4)
-        launch_kernel(k_pad_copy<uint32_t>, blocks, 256, 0, st, static_cast<const uint32_t*>(src),
-                      static_cast<uint32_t*>(dst), batches, srows, scols, drows, dcols);
-    else if (elem_bytes == 2)
-        launch_kernel(k_pad_copy<uint16_t>, blocks, 256, 0, st, static_cast<const uint16_t*>(src),
-                      static_cast<uint16_t*>(dst), batches, srows, scols, drows, dcols);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    PadJobs one{};
+    const hipError_t err = pad_jobs_add(one, elem_bytes, src, dst, batches, srows, scols, drows, dcols);
+    return err != hipSuccess ? err : launch_pad_jobs(one, st);
 }
 
 // Pair keys of a top-2 routing (see launch_pair_key): a token with one expert

@@ -237,6 +237,23 @@ hipError_t launch_residual_add(int dtype, const void* x, const void* f, void* ou
 // scols) or crops (drows <= srows, dcols <= scols).
 hipError_t launch_pad_copy(int elem_bytes, const void* src, void* dst, int64_t batches, int64_t srows,
                            int64_t scols, int64_t drows, int64_t dcols, hipStream_t st);
+// Several such copies as one launch (a layer on an unaligned shape pads up
+// to ten operands; a launch each cost 2 to 4 us).
+struct PadJob {
+    const void* src;
+    void* dst;
+    int64_t batches, srows, scols, drows, dcols;
+    int elem_bytes, blocks;
+};
+constexpr int kPadJobs = 10;
+struct PadJobs {
+    PadJob job[kPadJobs];
+    int n;
+};
+// Adds one copy (nothing for an empty destination).
+hipError_t pad_jobs_add(PadJobs& jobs, int elem_bytes, const void* src, void* dst, int64_t batches,
+                        int64_t srows, int64_t scols, int64_t drows, int64_t dcols);
+hipError_t launch_pad_jobs(const PadJobs& jobs, hipStream_t st);
 // Any row width D, one element per thread: xperm[p] = x[perm[p] / k] for
 // p < *nreal (a device count, e.g. offsets[E]; A = T k rows at most), and
 // the gated combine y[t] = sum_j gate[t, j] ye[inv[t k + j]] (as
