@@ -87,14 +87,14 @@ KERNEL_SOURCES = {
 
 def source_digest(kernel=None):
     """Hash of the HIP sources a kernel is built from (its own file and the shared
-    header; GEMM stages: gemm.hip), or of all of them: counters taken on other
+    header; GEMM stages: the gemm files), or of all of them: counters taken on other
     code are not reported."""
     h = hashlib.sha256()
     cdir = os.path.join(ROOT, "paper_2606_28516_amd", "csrc")
     if kernel is None:
         names = sorted(os.listdir(cdir))
     else:
-        names = sorted(KERNEL_SOURCES.get(kernel, ["gemm.hip"]) + ["kernels.h"])
+        names = sorted(KERNEL_SOURCES.get(kernel, ["gemm.hip", "gemm_bf16.h", "gemm_bf16.hip"]) + ["kernels.h"])
     for name in names:
         with open(os.path.join(cdir, name), "rb") as f:
             h.update(name.encode())
