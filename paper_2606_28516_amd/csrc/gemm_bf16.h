@@ -233,22 +233,23 @@ __device__ __forceinline__ uint32_t gb_b_offset(const GemmDesc& g, const GbParts
                   : kGbOob;
 }
 
-// Accumulators start at the bias of this lane's columns (nw: the wave's first
-// column); bias is only 4-byte aligned, which a buffer load allows.
 template <int TM, int TN>
-__device__ __forceinline__ void gb_init(const GemmDesc& g, int nw, int lh, f32x16 (&acc)[TM][TN]) {
+__device__ __forceinline__ void gb_zero(f32x16 (&acc)[TM][TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+}
+
+// Bias of column nw + lane (nw: the wave's first column; 0 past N or without a
+// bias), loaded before the k loop and added after it: a register a lane in
+// between.  An accumulator that starts at the bias rounds every partial sum
+// at the bias's magnitude.
+__device__ __forceinline__ float gb_bias(const GemmDesc& g, int nw, int lane) {
     const __amdgpu_buffer_rsrc_t rb = raw_rsrc(g.bias, g.bias != nullptr ? static_cast<int64_t>(g.N) * 4 : 0);
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int n = nw + j * 32 + 16 * (h >> 1) + 8 * lh + 4 * (h & 1);
-            const f32x4 b = __builtin_bit_cast(f32x4, raw_load16(rb, static_cast<uint32_t>(n) * 4u));
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[i][j][4 * h + t] = b[t];
-        }
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (nw + lane) * 4, 0, 0));
 }
 
 // Epilogue of one wave: local rows rw .. rw + 32 TM, columns nw .. nw + 32 TN.
@@ -256,10 +257,30 @@ __device__ __forceinline__ void gb_init(const GemmDesc& g, int nw, int lh, f32x1
 // values, 8 consecutive columns; N and ldc are multiples of 8, so a group is
 // all in or all out.  bfloat16 rows go through wb, 32 rows of this wave's own
 // LDS (16-byte chunks swizzled by the row), and leave as whole row pieces.
+// bias: gb_bias of this lane, handed to the lanes that hold its column through
+// the same LDS.
 template <int TM, int TN, int EPI>
 __device__ __forceinline__ void gb_epilogue(const GemmDesc& g, const GbTile& t, int rw, int nw, int lane,
-                                            unsigned char* wb, bool nt, f32x16 (&acc)[TM][TN]) {
+                                            unsigned char* wb, bool nt, float bias, f32x16 (&acc)[TM][TN]) {
     const int lrow = lane & 31, lh = lane >> 5;
+    static_assert(TN <= 2, "a lane for every column of the wave");
+    if constexpr (EPI != kEpiScale) {                             // a scaled product has no bias
+        reinterpret_cast<float*>(wb)[lane] = bias;
+        __builtin_amdgcn_wave_barrier();
+        f32x4 b4[TN][4];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                b4[j][h] = *reinterpret_cast<const f32x4*>(wb + 4 * (j * 32 + 16 * (h >> 1) + 8 * lh + 4 * (h & 1)));
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] += b4[j][v >> 2][v & 3];
+    }
     constexpr int RB = TN * 64, CH = RB / 16, RPI = 64 / CH;      // row bytes, chunks, rows per store
     static_assert(64 % CH == 0 && 32 % RPI == 0, "whole rows per store");
     if (EPI == kEpiPlain && g.c_f32) {
@@ -457,8 +478,9 @@ void k_gemm_bf16(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
             for (int i = 0; i < LPS; ++i) dma(s, s, i);
         }
 
+    const float bias = gb_bias(g, n0 + wn * TN * 32, lane);
     f32x16 acc[TM][TN];
-    gb_init(g, n0 + wn * TN * 32, lh, acc);
+    gb_zero(acc);
 
     // byte offsets of this lane's operand chunks of k step s within a stage
     const int bcol = gb_col_of_slot(lrow);
@@ -520,7 +542,7 @@ void k_gemm_bf16(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
     }
     gb_wait_barrier<0>();                       // the stage buffers are free
     gb_epilogue<TM, TN, EPI>(g, t, wm * TM * 32, n0 + wn * TN * 32, lane, smem + wave * (32 * TN * 64),
-                             nt_store != 0, acc);
+                             nt_store != 0, bias, acc);
 }
 
 // 256 x 256 tile over eight waves (2 x 4, each 128 x 64), two stages of 64 k:
@@ -590,8 +612,9 @@ void k_gemm_bf16_long(GemmDesc g, int mtiles, int ntiles, int group, int nt_stor
 #pragma unroll
         for (int i = 0; i < 4; ++i) dma_a(s, s, i);
     }
+    const float bias = gb_bias(g, n0 + wn * TN * 32, lane);
     f32x16 acc[TM][TN];
-    gb_init(g, n0 + wn * TN * 32, lh, acc);
+    gb_zero(acc);
 
     const int bcol = gb_col_of_slot(lrow);
     uint32_t oa[4], ob[4];
@@ -670,7 +693,7 @@ void k_gemm_bf16_long(GemmDesc g, int mtiles, int ntiles, int group, int nt_stor
     }
     gb_wait_barrier<0>();                        // the stage buffers are free
     gb_epilogue<TM, TN, EPI>(g, t, wm * TM * 32, n0 + wn * TN * 32, lane, smem + wave * (32 * TN * 64),
-                             nt_store != 0, acc);
+                             nt_store != 0, bias, acc);
 }
 
 // fc1 + GELU over many rows: 256 x 128 tile over four waves (2 x 2, each 128 x
@@ -733,8 +756,9 @@ void k_gemm_bf16_duo(GemmDesc g, int mtiles, int ntiles, int group, int nt_store
     };
     dma_a(0, 0);
     dma_b(0);
+    const float bias = gb_bias(g, n0 + wn * TN * 32, lane);
     f32x16 acc[TM][TN];
-    gb_init(g, n0 + wn * TN * 32, lh, acc);
+    gb_zero(acc);
 
     const int bcol = gb_col_of_slot(lrow);
     uint32_t oa[4], ob[4];
@@ -794,7 +818,7 @@ void k_gemm_bf16_duo(GemmDesc g, int mtiles, int ntiles, int group, int nt_store
     }
     gb_wait_barrier<0>();                        // the stage buffers are free
     gb_epilogue<TM, TN, kEpiGelu>(g, t, wm * TM * 32, n0 + wn * TN * 32, lane, smem + wave * (32 * TN * 64),
-                             nt_store != 0, acc);
+                             nt_store != 0, bias, acc);
 }
 
 template <int BM, int BN>

@@ -42,3 +42,46 @@ def test_dense_ffn_tiles(T, D, H):
     # the roundings are independent: over the whole result they stay near
     # sqrt(2) 2^-9 / sqrt(3), well under 2^-8
     assert ((y - ref).norm() / ref.norm()).item() <= 2.0 ** -8
+
+
+# one product of each tile: rows, columns, k; the tile its size selects
+TILES = [
+    (70, 72, 272),            # 64 x 64
+    (4000, 1544, 272),        # 128 x 128
+    (2000, 1032, 272),        # 128 x 128, deeper pipeline
+    (8000, 1544, 272),        # 256 x 256
+    (16000, 1032, 272),       # 320 x 256
+    (16000, 1544, 272),       # with a GELU: 256 x 128, two workgroups on a CU
+]
+
+
+@pytest.mark.parametrize("product", ["fc1", "fc2"])
+@pytest.mark.parametrize("M,N,K", TILES)
+def test_bias_is_added_to_the_finished_sum(M, N, K, product):
+    """A sum of 256 terms 2^-6 and, last in k, 2^24, plus a bias of -2^24: every
+    partial sum is a float32 value (4 after the small terms, 2^24 + 4 with the
+    large one), so the result is 4, exactly, where the bias is added last.
+    Next to a bias that comes first, -2^24, each 16 k's quarter is lost."""
+    dev = dict(device="cuda")
+    if product == "fc1":
+        x = torch.ones(M, K, **dev)
+        x[:, 256:] = 0
+        x[:, -1] = 2.0 ** 12
+        W1 = torch.full((N, K), 2.0 ** -6, **dev)
+        W1[:, -1] = 2.0 ** 12
+        b1, b2 = torch.full((N,), -2.0 ** 24, **dev), torch.zeros(K, **dev)
+        h = torch.arange(N, **dev)
+        W2 = (h % K == torch.arange(K, **dev)[:, None]).float()      # [K, N]: sums of whole z columns
+        want = (4.0 * W2.sum(1)).expand(M, K)                        # GELU(4) rounds to 4
+    else:
+        # z = 8 in 256 hidden units, 2^12 in the last one (GELU(v) = v there)
+        x, W1 = torch.zeros(M, N, **dev), torch.zeros(K, N, **dev)
+        b1 = torch.zeros(K, **dev)
+        b1[:256] = 8.0
+        b1[-1] = 2.0 ** 12
+        W2 = torch.full((N, K), 2.0 ** -9, **dev)
+        W2[:, -1] = 2.0 ** 12
+        b2 = torch.full((N,), -2.0 ** 24, **dev)
+        want = torch.full((M, N), 4.0, **dev)
+    y = cm.dense_ffn_forward(x.bfloat16(), W1.bfloat16(), b1, W2.bfloat16(), b2)
+    assert torch.equal(y.float(), want)
