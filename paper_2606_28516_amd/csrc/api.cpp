@@ -679,12 +679,15 @@ namespace {
 // dense FFN or a CLEAR-MoE layer whose last kernel writes each y row once
 // (top-1, top-2 in pair order; where the fused kernel runs, its variant with
 // the class rows), and operands whose byte offsets fit the bfloat16 products'
-// descriptors (class rows are dense_stride rows apart).
+// descriptors (class rows are dense_stride rows apart).  Without a basis and
+// residuals (r = q = 0) the y product has no k: the general kernel writes b2,
+// and the skip connection is a pass of its own.
 bool skip_in_layer(const clearmoe_shape& s, const clearmoe_router* rt) {
     if (s.dtype != CLEARMOE_BF16) return false;
     const int64_t stride = rt != nullptr ? rt->dense_stride : 0;
     if (rt != nullptr) {
         if (s.k != 1 && !pair_path(s)) return false;
+        if (s.r + s.q == 0) return false;
         if (fused_top1_supported(s.D, s.H, s.r, s.q) &&
             (s.k == 1 ? stride == 0 || fused_split(s.T, s.E, s.H) > 1 || !class_ffn_supported(s.D, s.H)
                       : rt->adaptive != 0))

@@ -23,6 +23,10 @@ CASES = [
     ("moe", 2000, 384, 1536, 4, 2, 128, 32, 197, True),     # adaptive: fused and pairs
     ("moe", 2000, 520, 1032, 4, 2, 64, 24, 197, True),      # adaptive: products only
     ("moe", 500, 128, 256, 16, 4, 32, 8, 0, False),         # the general path
+    ("moe", 300, 128, 256, 4, 1, 0, 0, 0, False),           # no basis, no residual: y = x + b2
+    ("moe", 300, 128, 256, 4, 1, 0, 0, 50, False),
+    ("moe", 300, 128, 256, 4, 2, 0, 0, 0, False),
+    ("moe", 300, 128, 256, 4, 2, 0, 0, 50, True),
 ]
 
 
