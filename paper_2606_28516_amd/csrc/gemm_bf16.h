@@ -220,17 +220,12 @@ __device__ __forceinline__ gb_i32x4 gb_a_desc(const GemmDesc& g, int64_t m_lo, i
 // start at multiples of 8 columns).
 __device__ __forceinline__ uint32_t gb_b_offset(const GemmDesc& g, const GbParts& p, int ng, int n, int kc,
                                                 gb_i32x4& d) {
-    const bf16_bits* base = p.b0;
-    int64_t ld = g.ldb;
-    int nb = 0, ne = g.n_split < g.N ? g.n_split : g.N;
-    if (ng >= g.n_split2) {
-        base = p.b2; ld = g.ldb2; nb = g.n_split2; ne = g.N;
-    } else if (ng >= g.n_split) {
-        base = p.b1; ld = g.ldb1; nb = g.n_split; ne = g.n_split2 < g.N ? g.n_split2 : g.N;
-    }
-    d = gb_desc(base, static_cast<int64_t>(ne - nb) * ld * 2);
-    return n < ne ? (static_cast<uint32_t>(n - nb) * static_cast<uint32_t>(ld) + static_cast<uint32_t>(kc)) * 2u
-                  : kGbOob;
+    const GemmBPart b = gemm_b_part(g.N, g.n_split, g.n_split2, ng);
+    const bf16_bits* base = b.part == 0 ? p.b0 : b.part == 1 ? p.b1 : p.b2;
+    const int64_t ld = b.part == 0 ? g.ldb : b.part == 1 ? g.ldb1 : g.ldb2;
+    d = gb_desc(base, static_cast<int64_t>(b.n1 - b.n0) * ld * 2);
+    return n < b.n1 ? (static_cast<uint32_t>(n - b.n0) * static_cast<uint32_t>(ld) + static_cast<uint32_t>(kc)) * 2u
+                    : kGbOob;
 }
 
 template <int TM, int TN>

@@ -344,6 +344,22 @@ inline GemmDesc gemm_desc(int64_t M, int N, int K) {
     return g;
 }
 hipError_t launch_gemm(int dtype, const GemmDesc& g, hipStream_t st);
+// The part of a B split along n (0, 1 or 2) that the eight columns from n = ng
+// on (a multiple of 8) are read from, and its columns [n0, n1).  Columns past N
+// (of a short last tile) take the part of the last eight: the part is never
+// one without columns, whose buffer descriptor would be empty (and its base
+// perhaps NULL) while the loads' scalar offset steps along k, so that a range
+// check which takes that offset off the size would wrap.
+struct GemmBPart {
+    int part, n0, n1;
+};
+__host__ __device__ inline GemmBPart gemm_b_part(int N, int n_split, int n_split2, int ng) {
+    if (ng > N - 8) ng = N - 8;
+    const int s1 = n_split < N ? n_split : N, s2 = n_split2 < N ? n_split2 : N;
+    if (ng >= s2) return GemmBPart{2, s2, N};
+    if (ng >= s1) return GemmBPart{1, s1, s2};
+    return GemmBPart{0, 0, s1};
+}
 // The bfloat16 products' own kernels (gemm_bf16.h), which launch_gemm uses
 // where they apply.
 bool gemm_bf16_supported(const GemmDesc& g);

@@ -1,10 +1,14 @@
 """The bfloat16 GEMM's tiles (csrc/gemm_bf16.h) through the dense FFN, at the
 sizes where they can go wrong: one row, one tile and one more row, rows, widths
 and k that end inside a tile or a stage, and each tile's range of sizes."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2606_28516_amd import clearmoe as cm
+from paper_2606_28516_amd import synth
+from tests.parity_util import BF16_FROB_REGRESS, assert_routing, frob_rel, gpu_ffn
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +89,22 @@ def test_bias_is_added_to_the_finished_sum(M, N, K, product):
         want = torch.full((M, N), 4.0, **dev)
     y = cm.dense_ffn_forward(x.bfloat16(), W1.bfloat16(), b1, W2.bfloat16(), b2)
     assert torch.equal(y.float(), want)
+
+
+@pytest.mark.parametrize("T,D,H,E,k,r,q", [
+    (300, 128, 1024, 4, 1, 40, 0),      # top-1 products without residual columns, N inside a tile
+    (300, 128, 1024, 4, 1, 0, 24),      # ... without basis columns
+    (300, 128, 1024, 4, 2, 40, 0),      # pair order
+    (300, 128, 1024, 4, 2, 0, 24),
+    (9001, 520, 1032, 4, 2, 392, 0),    # ... over 256-wide tiles
+])
+def test_layers_with_an_empty_part(T, D, H, E, k, r, q):
+    cfg = synth.LayerConfig("part", T=T, D=D, H=H, E=E, k=k, r=r, q=q, dtype="bf16", seed=T + r + q,
+                            residual="random", n_cal=2000)
+    L = synth.make_layer(cfg)
+    out = gpu_ffn(L)
+    rows = np.unique(np.random.default_rng(3).integers(0, T, 400))
+    tie = assert_routing(out["idx"], oracle.route(L["x"], L["Wg"], L["bg"], k)[2], k)
+    rows = rows[~tie[rows]]
+    ref = oracle.ffn_forward_layer(L, rows=rows)["y"]
+    assert frob_rel(out["y"][rows], ref) <= BF16_FROB_REGRESS
