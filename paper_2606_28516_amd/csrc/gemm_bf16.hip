@@ -92,18 +92,30 @@ bool fits(int64_t rows, int64_t ld) { return rows * ld * 2 < (int64_t{1} << 31);
 
 // Everything the layer asks for in bfloat16 but operands of 2 GiB and more
 // (32-bit offsets in the loads): rows of whole 16-byte pieces, parts of B at
-// multiples of 8, split along n or along k, and a scale or a bias or a GELU.
+// multiples of 8, split along n or along k, and a scale or a bias or a GELU
+// (split along k only a bias, and one row stride for parts 1 and 2).
 bool gemm_bf16_supported(const GemmDesc& g) {
     const bool part1 = g.n_split < g.N || g.k_split < g.K, part2 = g.n_split2 < g.N || g.k_split2 < g.K;
     if (g.K < 1 || g.N < 1 || g.M < 1 || g.M >= (int64_t{1} << 31)) return false;
     if (g.K % 8 != 0 || g.N % 8 != 0 || g.lda % 8 != 0 || g.ldc % 8 != 0) return false;
     if (g.n_split < 0 || g.n_split2 < g.n_split || g.k_split < 0 || g.k_split2 < g.k_split) return false;
     if (g.n_split % 8 != 0 || g.n_split2 % 8 != 0 || g.k_split % 8 != 0 || g.k_split2 % 8 != 0) return false;
-    if (gb_k_split(g) && (g.n_split < g.N || g.n_split2 < g.N)) return false;
+    if (gb_k_split(g)) {
+        if (g.n_split < g.N || g.n_split2 < g.N) return false;
+        if (g.gelu || g.row_scale != nullptr) return false;
+        if (part2 && g.ldb2 != g.ldb1) return false;
+    }
+    // k of each part: its rows hold as many elements (a load's scalar offset,
+    // the stage's k, then lies inside the descriptor of one column's row)
+    const int k1 = g.k_split < g.K ? g.k_split : g.K, k2 = g.k_split2 < g.K ? g.k_split2 : g.K;
+    const int kb1 = gb_k_split(g) ? k2 - k1 : g.K, kb2 = gb_k_split(g) ? g.K - k2 : g.K;
+    if (g.lda < g.K) return false;
     if (g.a_rows != nullptr ? (g.a_nrows < 1 || !fits(g.a_nrows, g.lda)) : !fits(512, g.lda)) return false;
-    if (g.n_split > 0 && g.k_split > 0 && (g.B == nullptr || g.ldb % 8 != 0 || !fits(g.N, g.ldb))) return false;
-    if (part1 && (g.B1 == nullptr || g.ldb1 % 8 != 0 || !fits(g.N, g.ldb1))) return false;
-    if (part2 && (g.B2 == nullptr || g.ldb2 % 8 != 0 || !fits(g.N, g.ldb2))) return false;
+    if (g.n_split > 0 && g.k_split > 0 &&
+        (g.B == nullptr || g.ldb % 8 != 0 || g.ldb < k1 || !fits(g.N, g.ldb)))
+        return false;
+    if (part1 && (g.B1 == nullptr || g.ldb1 % 8 != 0 || g.ldb1 < kb1 || !fits(g.N, g.ldb1))) return false;
+    if (part2 && (g.B2 == nullptr || g.ldb2 % 8 != 0 || g.ldb2 < kb2 || !fits(g.N, g.ldb2))) return false;
     if (g.row_scale != nullptr && (g.bias != nullptr || g.gelu || g.scale_col0 % 8 != 0 || g.scale_col1 % 8 != 0))
         return false;
     if (g.c_f32 && (g.gelu || g.row_scale != nullptr)) return false;
@@ -112,10 +124,7 @@ bool gemm_bf16_supported(const GemmDesc& g) {
 }
 
 hipError_t launch_gemm_bf16(const GemmDesc& g, hipStream_t st) {
-    if (gb_k_split(g)) {
-        if (g.gelu || g.row_scale != nullptr) return hipErrorInvalidValue;
-        return gb_launch<kEpiPlain, true>(g, st);
-    }
+    if (gb_k_split(g)) return gb_launch<kEpiPlain, true>(g, st);
     if (g.gelu)
         return gb_gelu_tiles(g) >= kGbDuoTiles ? gemm_bf16_duo(g, st) : gb_launch<kEpiGelu, false>(g, st);
     if (g.row_scale != nullptr) return gb_launch<kEpiScale, false>(g, st);

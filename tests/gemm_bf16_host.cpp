@@ -45,8 +45,56 @@ static void parts() {
             }
 }
 
+// A [r | q | q] product split along k, as the pair order's y product.
+static GemmDesc k_split_desc() {
+    static unsigned char mem[16];
+    GemmDesc g = gemm_desc(1000, 384, 128 + 2 * 32);
+    g.A = mem; g.lda = g.K;
+    g.B = mem; g.ldb = 128;
+    g.B1 = mem; g.ldb1 = 32;
+    g.B2 = mem; g.ldb2 = 32;
+    g.k_split = 128;
+    g.k_split2 = 128 + 32;
+    g.C = mem; g.ldc = g.N;
+    return g;
+}
+
+// What the bfloat16 kernels say they take, their launch takes and they compute.
+static void supported() {
+    const GemmDesc y = k_split_desc();
+    expect(gemm_bf16_supported(y), "a k split", 0, 0, 0, 0);
+    GemmDesc g = y;
+    g.gelu = 1;
+    expect(!gemm_bf16_supported(g), "a k split with a GELU", 0, 0, 0, 0);
+    g = y;
+    g.row_scale = reinterpret_cast<const float*>(g.A);
+    g.scale_rows = reinterpret_cast<const int32_t*>(g.A);
+    expect(!gemm_bf16_supported(g), "a k split with a scale", 0, 0, 0, 0);
+    g = y;
+    g.ldb2 = 40;                                         // the kernel has one row stride for parts 1 and 2
+    expect(!gemm_bf16_supported(g), "a k split with two row strides", 0, 0, 0, 0);
+    g = y;
+    g.k_split2 = g.K;                                    // [r | 2q]: one part less, its stride free
+    g.ldb1 = 64;
+    g.ldb2 = 0;
+    g.B2 = nullptr;
+    expect(gemm_bf16_supported(g), "a k split in two", 0, 0, 0, 0);
+    // rows shorter than the part: a load's scalar offset would leave the
+    // descriptor of a part of few columns
+    g = y;
+    g.ldb = 120;
+    expect(!gemm_bf16_supported(g), "short rows of B", 0, 0, 0, 0);
+    g = y;
+    g.ldb1 = g.ldb2 = 24;
+    expect(!gemm_bf16_supported(g), "short rows of B1 and B2", 0, 0, 0, 0);
+    g = y;
+    g.lda = g.K - 8;
+    expect(!gemm_bf16_supported(g), "short rows of A", 0, 0, 0, 0);
+}
+
 int main(int argc, char** argv) {
     if (argc > 1 && std::strcmp(argv[1], "parts") == 0) parts();
+    else if (argc > 1 && std::strcmp(argv[1], "supported") == 0) supported();
     else return 2;
     std::printf("%d violations\n", g_bad);
     return g_bad != 0;
