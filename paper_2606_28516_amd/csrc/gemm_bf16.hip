@@ -27,6 +27,7 @@ constexpr GbCost kGbCost[kGbTiles] = {
     {64, 64, 3, 3.0f, {{0.3f, 0.27f, 0.4f}, {1.1f, 0.39f, 0.4f}, {1.5f, 0.58f, 0.5f}}},
     {128, 128, 1, 0.7f, {{3.2f, 0.48f, 1.5f}}},
 };
+constexpr int kGbMostRows = 320;       // of the tallest tile
 constexpr int kCusPerXcd = 32;
 
 float gb_estimate(const GbCost& t, const GemmDesc& g, int stages) {
@@ -110,7 +111,9 @@ bool gemm_bf16_supported(const GemmDesc& g) {
     const int k1 = g.k_split < g.K ? g.k_split : g.K, k2 = g.k_split2 < g.K ? g.k_split2 : g.K;
     const int kb1 = gb_k_split(g) ? k2 - k1 : g.K, kb2 = gb_k_split(g) ? g.K - k2 : g.K;
     if (g.lda < g.K) return false;
-    if (g.a_rows != nullptr ? (g.a_nrows < 1 || !fits(g.a_nrows, g.lda)) : !fits(512, g.lda)) return false;
+    // a descriptor holds the rows of one tile, with a gather all of A
+    const int64_t rows = g.a_rows != nullptr ? g.a_nrows : (g.M < kGbMostRows ? g.M : kGbMostRows);
+    if (rows < 1 || !fits(rows, g.lda)) return false;
     if (g.n_split > 0 && g.k_split > 0 &&
         (g.B == nullptr || g.ldb % 8 != 0 || g.ldb < k1 || !fits(g.N, g.ldb)))
         return false;

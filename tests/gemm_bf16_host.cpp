@@ -92,9 +92,29 @@ static void supported() {
     expect(!gemm_bf16_supported(g), "short rows of A", 0, 0, 0, 0);
 }
 
+// Few rows far apart (class tokens of a long sequence: the class rows of z, H
+// times the stride apart) stay with the bfloat16 kernels as long as the rows of
+// one tile lie within 2 GiB.
+static void far_rows() {
+    static unsigned char mem[16];
+    for (int m : {1, 13, 320, 5000}) {
+        GemmDesc g = gemm_desc(m, 768, 3072);
+        g.A = mem;
+        g.B = mem; g.ldb = g.K;
+        g.C = mem; g.ldc = g.N;
+        const int64_t rows = m < 320 ? m : 320;          // of the tallest tile
+        const int64_t most = (int64_t{1} << 30) / rows;  // elements apart
+        g.lda = (most - 1) / 8 * 8;
+        expect(gemm_bf16_supported(g), "rows within 2 GiB", m, static_cast<int>(g.lda), 0, 0);
+        g.lda = (most + 7) / 8 * 8;
+        expect(!gemm_bf16_supported(g), "rows past 2 GiB", m, static_cast<int>(g.lda), 0, 0);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc > 1 && std::strcmp(argv[1], "parts") == 0) parts();
     else if (argc > 1 && std::strcmp(argv[1], "supported") == 0) supported();
+    else if (argc > 1 && std::strcmp(argv[1], "far_rows") == 0) far_rows();
     else return 2;
     std::printf("%d violations\n", g_bad);
     return g_bad != 0;

@@ -21,7 +21,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["parts", "supported"])
+@pytest.mark.parametrize("check", ["parts", "supported", "far_rows"])
 def test_host_rules(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr

@@ -108,3 +108,31 @@ def test_layers_with_an_empty_part(T, D, H, E, k, r, q):
     rows = rows[~tie[rows]]
     ref = oracle.ffn_forward_layer(L, rows=rows)["y"]
     assert frob_rel(out["y"][rows], ref) <= BF16_FROB_REGRESS
+
+
+@pytest.mark.parametrize("T,D,H,stride", [
+    (2900, 520, 3072, 700),      # five class rows of z 4.3 MB apart: 512 of them would span 2 GiB
+    (6000, 1544, 1032, 2999),    # three of them, 6.2 MB apart
+])
+def test_class_rows_far_apart(T, D, H, stride):
+    """Class tokens with a large stride on the product chain: the dense FFN's
+    output in their rows, the routed layer's in the others."""
+    cfg = synth.LayerConfig("far", T=T, D=D, H=H, E=4, k=1, r=40, q=24, dtype="bf16", seed=T, residual="random",
+                            n_cal=2000)
+    L = synth.make_layer(cfg)
+    rng = np.random.default_rng(T)
+    W2 = synth.to_bf16_bits((rng.standard_normal((D, H)) / H ** 0.5).astype(np.float32))
+    d = {n: cm.from_stored(v) for n, v in dict(L, W2=W2).items()
+         if n in ("x", "W1", "b1", "US", "Vt", "b2", "P", "Q", "Wg", "bg", "W2")}
+    w = [d[n] for n in ("x", "W1", "b1", "US", "Vt", "b2", "P", "Q")]
+    y = cm.ffn_forward_ex(*w, cm.make_router(d["Wg"], d["bg"], dense_stride=stride, W2=d["W2"]), 1)
+    plain = cm.ffn_forward_ex(*w, cm.make_router(d["Wg"], d["bg"]), 1)
+    cls = torch.arange(0, T, stride, device="cuda")
+    rest = torch.ones(T, dtype=torch.bool, device="cuda")
+    rest[cls] = False
+    assert torch.equal(y[rest], plain[rest])
+    z = torch.nn.functional.gelu(d["x"][cls].double() @ d["W1"].double().T + d["b1"].double())
+    ref = z @ d["W2"].double().T + d["b2"].double()
+    # as in test_dense_ffn_tiles: y rounded once from a sum over rounded z
+    bound = 2.0 ** -8 * (ref.abs() + z.abs() @ d["W2"].double().abs().T) + 1e-6
+    assert (y[cls].double() - ref).abs().le(bound).all()
