@@ -136,3 +136,50 @@ def test_class_rows_far_apart(T, D, H, stride):
     # as in test_dense_ffn_tiles: y rounded once from a sum over rounded z
     bound = 2.0 ** -8 * (ref.abs() + z.abs() @ d["W2"].double().abs().T) + 1e-6
     assert (y[cls].double() - ref).abs().le(bound).all()
+
+
+@pytest.mark.parametrize("T", [3, 16, 40])
+def test_dense_ffn_with_weights_of_2_gib(T):
+    """Weights past the loads' 32-bit offsets: the general kernel, with 64 x 128
+    tiles for few rows and 256 x 128 ones for more."""
+    D, H = 16384, 65536
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn(T, D, device="cuda", generator=g).bfloat16()
+    W1 = torch.empty(H, D, device="cuda", dtype=torch.bfloat16).normal_(0, D ** -0.5, generator=g)
+    W2 = torch.empty(D, H, device="cuda", dtype=torch.bfloat16).normal_(0, H ** -0.5, generator=g)
+    b1, b2 = 0.1 * torch.randn(H, device="cuda", generator=g), 0.1 * torch.randn(D, device="cuda", generator=g)
+    y = cm.dense_ffn_forward(x, W1, b1, W2, b2).double()
+    z = torch.nn.functional.gelu(x.double() @ W1.double().T + b1.double())
+    W2 = W2.double()
+    ref = z @ W2.T + b2.double()
+    # as in test_dense_ffn_tiles
+    bound = 2.0 ** -8 * (ref.abs() + z.abs() @ W2.abs().T) + 1e-6
+    assert (y - ref).abs().le(bound).all()
+    assert ((y - ref).norm() / ref.norm()).item() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("k,r,q", [(1, 40, 24), (1, 136, 24), (2, 136, 24)])
+def test_layers_with_z_of_2_gib(k, r, q):
+    """z [T, H] past the loads' 32-bit offsets: the [t|u] products gather its
+    rows with the general kernel (128 x 64 and 256 x 128 tiles, grouped, scaled
+    columns, parts of B), the others stay with the bfloat16 kernels."""
+    T, D, H, E = 16421, 144, 65536, 4
+    g = torch.Generator(device="cuda").manual_seed(r + k)
+    n = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    x, W1, b1, b2 = n(T, D).bfloat16(), (n(H, D) / D ** 0.5).bfloat16(), 0.1 * n(H), 0.1 * n(D)
+    US, Vt = (n(D, r) / r ** 0.5).bfloat16(), (n(r, H) / H ** 0.5).bfloat16()
+    P, Q = (n(E, D, q) / q ** 0.5).bfloat16(), (n(E, q, H) / H ** 0.5).bfloat16()
+    Wg, bg = (n(E, D) / D ** 0.5).bfloat16(), 0.1 * n(E)
+    idx = torch.empty(T, k, device="cuda", dtype=torch.int32)
+    gate = torch.empty(T, k, device="cuda")
+    y = cm.ffn_forward(x, W1, b1, US, Vt, b2, P, Q, Wg, bg, k, idx_out=idx, gate_out=gate)
+    rows = torch.cat([torch.arange(0, T, 41, device="cuda"), torch.arange(T - 40, T, device="cuda")]).unique()
+    z = torch.nn.functional.gelu(x[rows].double() @ W1.double().T + b1.double())
+    ref = (z @ Vt.double().T) @ US.double().T + b2.double()
+    for j in range(k):
+        for e in range(E):
+            at = (idx[rows, j] == e).nonzero().flatten()
+            u = gate[rows[at], j:j + 1].double() * (z[at] @ Q[e].double().T)
+            ref[at] += u @ P[e].double().T
+    err = (y[rows].double() - ref).norm() / ref.norm()
+    assert err.item() <= BF16_FROB_REGRESS
