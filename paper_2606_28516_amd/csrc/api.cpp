@@ -91,7 +91,9 @@ Layout layout(const clearmoe_shape& s) {
     }
     // float32 partials and per-tile arrival counters: of the fused top-1
     // kernel's hidden split (small batches), or else, on the top-1 GEMM
-    // chain, of the [t|u] product's split K
+    // chain, of the [t|u] product's split K in float32 (in bfloat16 nothing
+    // reads them; they are kept so that the workspace, and what fits the
+    // no-allocation variant's array, are the same in both types)
     // (a top-2 pair order's single-expert tokens take the top-1 path)
     const bool fused_ok = s.dtype == CLEARMOE_BF16 && fused_top1_supported(s.D, s.H, s.r, s.q);
     const bool top1 = k == 1 || pair_path(s);
@@ -823,11 +825,11 @@ int ffn_forward_impl(const clearmoe_shape* shape, const clearmoe_router* router,
     // when it is small enough for one workgroup's scan; the pair order
     // dispatches pair keys instead, below)
     // the router also clears the counters that the fused kernel's hidden split
-    // or the grouped products' split K will count arrivals in
+    // or the float32 [t|u] product's split K will count arrivals in
     const bool top1_rows = s.k == 1 || (router->adaptive && pair_path(s));
     const bool fused_rows = s.dtype == CLEARMOE_BF16 && fused_top1_supported(s.D, s.H, s.r, s.q);
     const int nzero = !top1_rows ? 0
-                      : !fused_rows ? kGemmKsplitTiles
+                      : !fused_rows ? (s.dtype == CLEARMOE_F32 ? kGemmKsplitTiles : 0)
                       : fused_split(T, s.E, s.H) > 1 ? static_cast<int>(fused_counters(T, s.E)) : 0;
     rc = route_impl(s, L, *router, x, idx, gate, ws, st, at<int32_t>(ws, L.fcount), nzero);
     if (rc != CLEARMOE_OK) return rc;

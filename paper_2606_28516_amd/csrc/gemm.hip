@@ -136,7 +136,8 @@ void k_gemm(GemmDesc g, int mtiles, int ntiles, int group, int ksplit, int stage
     //      its bound M -- spread over every XCD.  With split K, S consecutive
     //      workgroups of one XCD share a tile, part kp taking its share of
     //      the k stages.
-    const int S = g.ks_part != nullptr ? ksplit : 1;
+    constexpr bool kSplitK = sizeof(Tin) == 4;   // only float32 products split K (gemm_cfg)
+    const int S = kSplitK && g.ks_part != nullptr ? ksplit : 1;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     const int tile_local = local / S, kp = local - tile_local * S;
     const int mx = (mtiles - xcd + kXcds - 1) / kXcds;
@@ -346,7 +347,7 @@ void k_gemm(GemmDesc g, int mtiles, int ntiles, int group, int ksplit, int stage
     //      and counts itself in; the last part of the tile to arrive sums the
     //      S parts in part order (the same bits whichever part is last) and
     //      runs the epilogue.  The parts of a tile share an XCD.
-    if (S > 1) {
+    if (kSplitK && S > 1) {
         constexpr int kDevScope = 16;   // cache-policy bits: sc1
         constexpr int kTiles = TM * TN;
         const __amdgpu_buffer_rsrc_t rp = raw_rsrc(
@@ -529,8 +530,10 @@ static hipError_t gemm_cfg(const GemmDesc& g, hipStream_t st) {
     constexpr int BK = SB / static_cast<int>(sizeof(Tin));
     // tiles x S <= 256 parts of BM x BN floats each fit kGemmKsplitBytes up
     // to 64 x 128 tiles (larger ones never have so few tiles here)
+    // (float32 only: the bfloat16 products have kernels of their own, and those
+    // with 2 GiB of operands, which come here, have tiles for every CU)
     int S = 1;
-    if (g.ks_part != nullptr && g.ks_count != nullptr && BM * BN <= 64 * 128)
+    if (sizeof(Tin) == 4 && g.ks_part != nullptr && g.ks_count != nullptr && BM * BN <= 64 * 128)
         S = gemm_ksplit(tiles, (g.K + BK - 1) / BK);
     GemmDesc d = g;
     if (S == 1) d.ks_part = nullptr;

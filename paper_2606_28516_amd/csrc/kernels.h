@@ -319,7 +319,7 @@ struct GemmDesc {
     int N, K;
     const int32_t* seg_offsets;  // optional [nseg+1] on the device: grouped GEMM
     int nseg;
-    // optional split K for products with few tiles and long K (see
+    // optional split K for float32 products with few tiles and long K (see
     // gemm_ksplit): float32 partial tiles (kGemmKsplitBytes) and per-tile
     // arrival counters (kGemmKsplitTiles int32, zero before the launch) of
     // workspace

@@ -1,11 +1,12 @@
-"""GPU parity of the top-1 GEMM chain's [t|u] product when it splits K.
+"""GPU parity of the top-1 GEMM chain's [t|u] product with few tiles and a
+long K.
 
-With few tiles and a long K (the DeiT-Tiny float32 layer: 58 tiles of 64x64,
-24 k stages), the grouped [t|u] product runs as S parts per tile whose float32
-partial tiles go to the workspace; the last part to arrive sums them in part
-order.  Checked against the fp64 oracle in float32 and bfloat16 (r off the
-fused kernel's 32-grid, so the GEMM chain runs), and bit for bit across calls
-that reuse one workspace filled with 0xFF first.
+In float32 (the DeiT-Tiny layer: 58 tiles of 64x64, 24 k stages) the grouped
+product then splits K: S parts per tile whose float32 partial tiles go to the
+workspace; the last part to arrive sums them in part order.  In bfloat16 (r
+off the fused kernel's 32-grid, so the GEMM chain runs) the product has a
+kernel of its own, which never splits K.  Both against the fp64 oracle, and
+bit for bit across calls that reuse one workspace filled with 0xFF first.
 """
 import numpy as np
 import pytest
@@ -22,8 +23,8 @@ SPLIT_LAYERS = [
     # dt, T, D, H, E, r, q
     ("f32", 1576, 192, 768, 4, 64, 16),     # DeiT-Tiny widths: S = 4
     ("f32", 70, 64, 2048, 3, 32, 8),        # 4 tiles of 128x64, 64 k stages: S = 8
-    ("bf16", 300, 128, 1024, 4, 48, 16),    # r % 32 != 0: GEMM chain, 7 tiles, S = 4
-    ("bf16", 300, 128, 2056, 4, 48, 16),    # K >= 2048: the staged epilogue after the part sum
+    ("bf16", 300, 128, 1024, 4, 48, 16),    # r % 32 != 0: GEMM chain, 64 x 64 tiles, whole k stages
+    ("bf16", 300, 128, 2056, 4, 48, 16),    # a last k stage of 8
 ]
 
 
