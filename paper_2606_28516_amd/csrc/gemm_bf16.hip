@@ -12,7 +12,7 @@ namespace {
 // workgroups of a CU in a round (at most per_cu) and c = fixed + stage * (k
 // stages) + gelu.  Picking the smallest estimate costs 1.1 % over the best of
 // nine tiles on that sweep, and 2.3 % without the last tile.
-enum GbTileId { kTile320, kTile256Long, kTile128, kTile64, kTile128Deep, kGbTiles };
+constexpr int kGbTiles = kTileDuo;     // those the estimate chooses from
 struct GbCost {
     int bm, bn, per_cu;
     float base;
@@ -64,18 +64,7 @@ int64_t gb_gelu_tiles(const GemmDesc& g) { return ((g.M + 255) / 256) * ((g.N + 
 
 template <int EPI, bool KS3>
 hipError_t gb_launch(const GemmDesc& g, hipStream_t st) {
-    const int stages = gb_stages(g);
-    int best = -1;
-    float t = 0.0f;
-    for (int i = 0; i < kGbTiles; ++i) {
-        if (KS3 && i == kTile256Long) continue;
-        const float e = gb_estimate(kGbCost[i], g, stages);
-        if (best < 0 || e < t) {
-            best = i;
-            t = e;
-        }
-    }
-    switch (best) {
+    switch (gemm_bf16_tile(g)) {
         case kTile320: return gemm_bf16_cfg<2, 4, 5, 2, 2, 2, EPI, KS3>(g, st);
         case kTile256Long:
             if constexpr (!KS3) return gemm_bf16_long<EPI>(g, st);
@@ -126,10 +115,25 @@ bool gemm_bf16_supported(const GemmDesc& g) {
     return g.seg_offsets == nullptr || g.seg_merge || g.nseg <= 64;
 }
 
+GemmBf16Tile gemm_bf16_tile(const GemmDesc& g) {
+    if (g.gelu && gb_gelu_tiles(g) >= kGbDuoTiles) return kTileDuo;
+    const int stages = gb_stages(g);
+    int best = -1;
+    float t = 0.0f;
+    for (int i = 0; i < kGbTiles; ++i) {
+        if (gb_k_split(g) && i == kTile256Long) continue;
+        const float e = gb_estimate(kGbCost[i], g, stages);
+        if (best < 0 || e < t) {
+            best = i;
+            t = e;
+        }
+    }
+    return static_cast<GemmBf16Tile>(best);
+}
+
 hipError_t launch_gemm_bf16(const GemmDesc& g, hipStream_t st) {
     if (gb_k_split(g)) return gb_launch<kEpiPlain, true>(g, st);
-    if (g.gelu)
-        return gb_gelu_tiles(g) >= kGbDuoTiles ? gemm_bf16_duo(g, st) : gb_launch<kEpiGelu, false>(g, st);
+    if (g.gelu) return gemm_bf16_tile(g) == kTileDuo ? gemm_bf16_duo(g, st) : gb_launch<kEpiGelu, false>(g, st);
     if (g.row_scale != nullptr) return gb_launch<kEpiScale, false>(g, st);
     return gb_launch<kEpiPlain, false>(g, st);
 }

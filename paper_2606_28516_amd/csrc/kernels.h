@@ -363,6 +363,10 @@ __host__ __device__ inline GemmBPart gemm_b_part(int N, int n_split, int n_split
 // The bfloat16 products' own kernels (gemm_bf16.h), which launch_gemm uses
 // where they apply.
 bool gemm_bf16_supported(const GemmDesc& g);
+// The tile a supported product runs on (rows x columns; Long, Deep: with the
+// loads issued further ahead; Duo: 256 x 128, two workgroups on a CU).
+enum GemmBf16Tile { kTile320, kTile256Long, kTile128, kTile64, kTile128Deep, kTileDuo };
+GemmBf16Tile gemm_bf16_tile(const GemmDesc& g);
 hipError_t launch_gemm_bf16(const GemmDesc& g, hipStream_t st);
 
 // Fused top-1 layer in bfloat16: y[perm p] = [t|u](p) [US | P_e]^T + b2 with

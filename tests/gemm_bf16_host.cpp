@@ -1,6 +1,7 @@
 // Checks of the bfloat16 GEMM's host-side and address rules on the CPU, run by
 // test_gemm_bf16_host.py.  Prints each violation; exits with 1 if any.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "kernels.h"
@@ -111,7 +112,25 @@ static void far_rows() {
     }
 }
 
+// The tile of each product in argv: M N K gelu nseg k_split k_split2 (nseg 0:
+// not grouped).
+static int tiles(int n, char** v) {
+    static const char* names[] = {"320", "256 long", "128", "64", "128 deep", "duo"};
+    static int32_t seg[1];
+    for (int i = 0; i + 6 < n; i += 7) {
+        GemmDesc g = gemm_desc(std::atoll(v[i]), std::atoi(v[i + 1]), std::atoi(v[i + 2]));
+        g.gelu = std::atoi(v[i + 3]);
+        g.nseg = std::atoi(v[i + 4]);
+        g.seg_offsets = g.nseg > 0 ? seg : nullptr;
+        g.k_split = std::atoi(v[i + 5]);
+        g.k_split2 = std::atoi(v[i + 6]);
+        std::printf("%s\n", names[gemm_bf16_tile(g)]);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
+    if (argc > 1 && std::strcmp(argv[1], "tiles") == 0) return tiles(argc - 2, argv + 2);
     if (argc > 1 && std::strcmp(argv[1], "parts") == 0) parts();
     else if (argc > 1 && std::strcmp(argv[1], "supported") == 0) supported();
     else if (argc > 1 && std::strcmp(argv[1], "far_rows") == 0) far_rows();

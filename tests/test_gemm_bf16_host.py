@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_2606_28516_amd import build as hb
+from tests import test_gpu_gemm_bf16 as gpu
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -25,3 +26,29 @@ def program(tmp_path_factory):
 def test_host_rules(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def _tiles(program, products):
+    args = [str(v) for p in products for v in p]
+    return subprocess.run([program, "tiles", *args], capture_output=True, text=True, check=True,
+                          timeout=60).stdout.splitlines()
+
+
+ALL = {"64", "128", "128 deep", "256 long", "320", "duo"}
+
+
+def test_gpu_sizes_cover_every_tile(program):
+    """What test_gpu_gemm_bf16.py says about its sizes."""
+    fc1 = _tiles(program, [(T, H, D, 1, 0, D, D) for T, D, H in gpu.SIZES])
+    fc2 = _tiles(program, [(T, D, H, 0, 0, H, H) for T, D, H in gpu.SIZES])
+    assert set(fc1) == ALL and set(fc2) == ALL - {"duo"}
+    # the sizes with a short last tile in rows, columns and k
+    ragged = [(T, D, H) for T, D, H in gpu.SIZES if T % 64 and D % 64 and H % 64]
+    assert {"320", "256 long"} <= set(_tiles(program, [(T, H, D, 1, 0, D, D) for T, D, H in ragged]))
+    want = ["64", "128", "128 deep", "256 long", "320", "duo"]
+    assert _tiles(program, [(M, N, K, 1, 0, K, K) for M, N, K in gpu.TILES]) == want
+    assert _tiles(program, [(M, N, K, 0, 0, K, K) for M, N, K in gpu.TILES])[:5] == want[:5]
+    for T, D, H, E, r, q, y, tu in gpu.GROUPED:
+        pairs = E * (E - 1) // 2
+        assert _tiles(program, [(T, D, r + q, 0, E, r, r + q), (T, D, r + 2 * q, 0, pairs, r, r + q)]) == [y, y]
+        assert _tiles(program, [(T, r + 2 * q, H, 0, pairs, H, H)]) == [tu]

@@ -1,6 +1,7 @@
-"""The bfloat16 GEMM's tiles (csrc/gemm_bf16.h) through the dense FFN, at the
-sizes where they can go wrong: one row, one tile and one more row, rows, widths
-and k that end inside a tile or a stage, and each tile's range of sizes."""
+"""The bfloat16 GEMM's tiles (csrc/gemm_bf16.h) through the dense FFN and the
+layers, at the sizes where they can go wrong: one row, one tile and one more
+row, rows, widths and k that end inside a tile or a stage, grouped rows, and
+each tile (test_gemm_bf16_host.py checks which tiles the sizes select)."""
 import numpy as np
 import pytest
 import torch
@@ -26,6 +27,9 @@ SIZES = [
     (16129, 64, 1536),        # ... one k stage, one row in the last row tile
     (8449, 320, 2944),        # ... an odd number of k stages
     (8192, 1032, 3072),       # ... a last stage of 8 k
+    (16003, 1032, 1032),      # 320 x 256 twice, with short last tiles and a last stage of 8 k
+    (9003, 520, 1544),        # 256 x 256 with short last tiles
+    (2001, 264, 1032),        # fc1 on the deeper 128 x 128 tiles
 ]
 
 
@@ -52,7 +56,7 @@ def test_dense_ffn_tiles(T, D, H):
 TILES = [
     (70, 72, 272),            # 64 x 64
     (4000, 1544, 272),        # 128 x 128
-    (2000, 1032, 272),        # 128 x 128, deeper pipeline
+    (2000, 1032, 520),        # 128 x 128, deeper pipeline
     (8000, 1544, 272),        # 256 x 256
     (16000, 1032, 272),       # 320 x 256
     (16000, 1544, 272),       # with a GELU: 256 x 128, two workgroups on a CU
@@ -174,12 +178,48 @@ def test_layers_with_z_of_2_gib(k, r, q):
     gate = torch.empty(T, k, device="cuda")
     y = cm.ffn_forward(x, W1, b1, US, Vt, b2, P, Q, Wg, bg, k, idx_out=idx, gate_out=gate)
     rows = torch.cat([torch.arange(0, T, 41, device="cuda"), torch.arange(T - 40, T, device="cuda")]).unique()
+    ref = _layer_rows(rows, x, W1, b1, US, Vt, b2, P, Q, idx, gate)
+    err = (y[rows].double() - ref).norm() / ref.norm()
+    assert err.item() <= BF16_FROB_REGRESS
+
+
+def _layer_rows(rows, x, W1, b1, US, Vt, b2, P, Q, idx, gate):
+    """Rows of the layer in 64 bits, with the experts and gates given."""
     z = torch.nn.functional.gelu(x[rows].double() @ W1.double().T + b1.double())
     ref = (z @ Vt.double().T) @ US.double().T + b2.double()
-    for j in range(k):
-        for e in range(E):
+    for j in range(idx.shape[1]):
+        for e in range(P.shape[0]):
             at = (idx[rows, j] == e).nonzero().flatten()
             u = gate[rows[at], j:j + 1].double() * (z[at] @ Q[e].double().T)
             ref[at] += u @ P[e].double().T
-    err = (y[rows].double() - ref).norm() / ref.norm()
-    assert err.item() <= BF16_FROB_REGRESS
+    return ref
+
+
+GROUPED = [
+    # T, D, H, E, r, q; tiles of the y products (split along k, rows scattered)
+    # and of the pair order's [t|u_a|u_b] (parts along n, scaled, rows gathered)
+    (11003, 1032, 520, 4, 136, 24, "320", "128 deep"),
+    (20011, 776, 520, 4, 264, 72, "128", "256 long"),
+]
+
+
+@pytest.mark.parametrize("k", [1, 2])
+@pytest.mark.parametrize("T,D,H,E,r,q", [c[:6] for c in GROUPED])
+def test_grouped_products_on_tall_tiles(T, D, H, E, r, q, k):
+    g = torch.Generator(device="cuda").manual_seed(T + k)
+    n = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    x, W1, b1, b2 = n(T, D).bfloat16(), (n(H, D) / D ** 0.5).bfloat16(), 0.1 * n(H), 0.1 * n(D)
+    US, Vt = (n(D, r) / r ** 0.5).bfloat16(), (n(r, H) / H ** 0.5).bfloat16()
+    P, Q = (n(E, D, q) / q ** 0.5).bfloat16(), (n(E, q, H) / H ** 0.5).bfloat16()
+    Wg, bg = (n(E, D) / D ** 0.5).bfloat16(), 0.1 * n(E)
+    idx = torch.empty(T, k, device="cuda", dtype=torch.int32)
+    gate = torch.empty(T, k, device="cuda")
+    y = cm.ffn_forward(x, W1, b1, US, Vt, b2, P, Q, Wg, bg, k, idx_out=idx, gate_out=gate)
+    rows = torch.arange(T, device="cuda")
+    ref = _layer_rows(rows, x, W1, b1, US, Vt, b2, P, Q, idx, gate)
+    err = (y.double() - ref).norm(dim=1) / ref.norm(dim=1)      # every row of every segment
+    assert err.max().item() <= BF16_FROB_REGRESS
+    # and with the skip connection in the y product
+    layer = cm.make_stack_layer(W1, b1, b2, US=US, Vt=Vt, P=P, Q=Q, router=cm.make_router(Wg, bg), k=k)
+    skip = cm.stack_forward(x, [layer], H, E, r, q, residual=True)
+    assert torch.equal(skip, (x.float() + y.float()).bfloat16())

@@ -363,18 +363,18 @@ def test_dense_comparator(name):
 
 
 @pytest.mark.parametrize("T,D,H", [
-    (20011, 1672, 1032),   # both products: 256x128 tiles, 64-byte stages (largest)
-    (16411, 520, 1032),    # both products: 256x128 tiles by row count (M >= 16384)
-    (16411, 264, 1032),    # fc2 (N = 264, K = 1032): 256x128 tiles, long K with N <= 512
-    (5003, 136, 1032),     # fc1 (N = 1032, K = 136): 128x128 tiles over eight waves
-    (20011, 1672, 2056),   # fc2 with K >= 2048: 256x128 tiles, the staged epilogue, last column tile 8 wide
-    (9001, 264, 2056),     # fc2 (N = 264, K = 2056): 64x64 tiles, the staged epilogue
+    (20011, 1672, 1032),   # fc1: 256x256 tiles, fc2: 320x256
+    (16411, 520, 1032),    # a last column tile 8 wide in both products
+    (16411, 264, 1032),    # fc2: N = 264
+    (5003, 136, 1032),     # fc1: K = 136, a last k stage of 8
+    (20011, 1672, 2056),   # fc1: 256x128 tiles, two workgroups on a CU; fc2: 320x256, K = 2056
+    (9001, 264, 2056),     # both products: 128x128 tiles
 ])
 def test_dense_gemm_tile_rules_ragged(T, D, H):
-    """The dense FFN (bf16) at shapes that select each bf16 tile rule of the
-    GEMM, with ragged row, column and k edges (no dimension a multiple of the
-    tile; K ends inside a 32-element stage).  Sampled rows against the oracle,
-    to which the dense FFN reduces with US = I, Vt = W2 and no residual."""
+    """The dense FFN (bf16) over large shapes with ragged row, column and k
+    edges (no dimension a multiple of the tile; K ends inside a 64-element
+    stage).  Sampled rows against the oracle, to which the dense FFN reduces
+    with US = I, Vt = W2 and no residual."""
     rng = np.random.default_rng(T + D)
     x = synth.to_bf16_bits(rng.standard_normal((T, D)).astype(np.float32))
     W1 = synth.to_bf16_bits((0.02 * rng.standard_normal((H, D))).astype(np.float32))
@@ -396,11 +396,12 @@ def test_dense_gemm_tile_rules_ragged(T, D, H):
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_large_fc1_tiles_with_ragged_edges(dt):
     """fc1 of this layer (M = T = 52517, N = H = 1032, K = D = 72) has
-    206 x 5 = 1030 tiles of 256 x 256, which selects the product's 8-wave
-    large-tile configuration; the last row tile holds 37 rows, the last
-    column tile 8 columns, and K ends inside its second 128-byte stage.
-    Top-2, so the layer runs the GEMM chain.  Routing on every token, values
-    on a sample of rows."""
+    206 x 5 = 1030 tiles of 256 x 256: in float32 that selects the product's
+    8-wave large-tile configuration, in bfloat16 (206 x 9 tiles of 256 x 128)
+    the one with two workgroups on a CU; the last row tile holds 37 rows, the
+    last column tile 8 columns, and K ends inside its last stage.  Top-2, so
+    the layer runs the GEMM chain.  Routing on every token, values on a sample
+    of rows."""
     cfg = synth.LayerConfig("bigtile", T=52517, D=72, H=1032, E=4, k=2, r=32, q=8, dtype=dt,
                             seed=11, residual="random", n_cal=2000)
     L = synth.make_layer(cfg)
