@@ -16,9 +16,11 @@
  *     resources that an entry point creates on first use and keeps until
  *     the process ends: clearmoe_ffn_forward_padded, a pinned 256-byte host
  *     buffer per calling thread (and an event per call, destroyed before it
- *     returns); clearmoe_ffn_forward_ex with class tokens on a small batch, a
- *     side stream and two events per device (clearmoe_ffn_forward_noalloc
- *     creates none); the stage timer, the events it is started with.
+ *     returns); clearmoe_ffn_forward_ex and clearmoe_stack_forward where a
+ *     top-1 bfloat16 layer with class tokens runs on the fused kernel with
+ *     its hidden width split (small batches), a side stream and two events
+ *     per device (clearmoe_ffn_forward_noalloc creates none); the stage
+ *     timer, the events it is started with.
  *   - Matrices are row-major and contiguous.  Weights are stored [out, in]
  *     (the nn.Linear convention), so every product is A[M,K] B[N,K]^T.
  *   - x, W1, US, Vt, P, Q, Wg, ye and y have element type shape->dtype
@@ -223,7 +225,9 @@ int clearmoe_combine(const clearmoe_shape* shape, const void* ye, const int32_t*
  * rank-r / rank-q projections are rounded to bfloat16 between products.
  * For k = 1 the shared basis and the residual run as two products over the
  * expert order ([t|u] = z[perm] [Vt;Q_e]^T, then y[perm] = [t|u] [US|P_e]^T
- * + b2); for k > 1 h_sh and h_res are formed apart and combined. */
+ * + b2), and so do those of a top-2 layer with up to ten experts over the
+ * tokens in order of their expert pair; otherwise h_sh and h_res are formed
+ * apart and combined. */
 int clearmoe_ffn_forward(const clearmoe_shape* shape, const void* x, const void* W1,
                          const float* b1, const void* US, const void* Vt, const float* b2,
                          const void* P, const void* Q, const void* Wg, const float* bg, void* y,
@@ -247,7 +251,7 @@ int clearmoe_ffn_forward(const clearmoe_shape* shape, const void* x, const void*
  * intermediates.  A shape that needs more than the array returns
  * CLEARMOE_ERR_TOO_LARGE before anything is launched.  Every call on a device
  * shares that device's array and leaves its contents behind (the counters it
- * needs are cleared by the call's own fill kernels): calls that overlap in
+ * needs are cleared by the call's own router kernel): calls that overlap in
  * time on one device -- on different streams or threads -- race and must
  * not be issued. */
 int clearmoe_ffn_forward_noalloc(const clearmoe_shape* shape, const void* x, const void* W1,
@@ -334,7 +338,8 @@ enum {
     CLEARMOE_STAGE_PAIR_KEY = 16,      /* top-2: expert-pair keys and gates */
     CLEARMOE_STAGE_TU_PAIR = 17,       /* top-2: [t|u_a|u_b] grouped by expert pair */
     CLEARMOE_STAGE_Y_PAIR = 18,        /* top-2: y grouped by pair, rows scattered */
-    CLEARMOE_STAGE_RESIDUAL_ADD = 19,  /* stack: x_{l+1} = x_l + f_l(x_l) */
+    CLEARMOE_STAGE_RESIDUAL_ADD = 19,  /* stack: x_{l+1} = x_l + f_l(x_l), for the layers whose
+                                          last kernel does not add it */
     CLEARMOE_N_STAGES = 20
 };
 

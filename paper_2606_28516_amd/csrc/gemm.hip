@@ -3,7 +3,9 @@
 // used for fc1 + GELU (Eq. 2), the two skinny products of the shared SVD basis
 // and, grouped by expert with device-resident segment offsets, the two
 // products of the per-expert residual (Algorithm 3: one product per
-// contiguous expert sub-batch, here with no host round trip for the sizes).
+// contiguous expert sub-batch, here with no host round trip for the sizes),
+// in float32; in bfloat16 for what gemm_bf16.h leaves (operands of 2 GiB and
+// more, no k).
 //
 // Mapping
 //   * 4 or 8 waves in a WM x WN grid; a wave owns a (BM/WM) x (BN/WN)
@@ -539,10 +541,11 @@ static hipError_t gemm_cfg(const GemmDesc& g, hipStream_t st) {
     if (S == 1) d.ks_part = nullptr;
     // every XCD takes ceil(mt / 8) row tiles of nt tiles of S parts
     const int64_t per_xcd = (mt + kXcds - 1) / kXcds * nt * S;
-    // measured on the DeiT-Base products: groups of four row tiles (fc1 +
-    // GELU 391 -> 377 us, the others unchanged); the staged epilogue pays
-    // off for long K (dense fc2 298 -> 288, pair [t|u] product 183 -> 178 us)
-    // and costs for short K (fc1 +1 %, DeiT-Small fc1 +5 %)
+    // measured on the DeiT-Base products in bfloat16, which ran here before
+    // they had kernels of their own: groups of four row tiles (fc1 + GELU 391
+    // -> 377 us, the others unchanged); the staged epilogue pays off for long
+    // K (dense fc2 298 -> 288, pair [t|u] product 183 -> 178 us) and costs for
+    // short K (fc1 +1 %, DeiT-Small fc1 +5 %)
     const int group = 4, staged = g.K >= 2048 ? 1 : 0;
     const int64_t grid = per_xcd * kXcds;
     launch_kernel(k_gemm<Tin, BM, BN, WM, WN, NS, SB, WPE>, dim3(static_cast<unsigned>(grid)), 64 * WM * WN, 0, st,
@@ -553,10 +556,9 @@ static hipError_t gemm_cfg(const GemmDesc& g, hipStream_t st) {
 // Tile choice by shape (measured on MI355X at the layer's sizes): with few
 // 128x128 tiles the GEMM is latency bound, so 64-row tiles (more workgroups
 // per CU) win; long-K skinny products want 64x64 with four stages in flight;
-// the large bfloat16 products take 256x128 tiles over 8 waves with 64-byte
-// stages (two workgroups per CU), and large float32 ones 256x256 tiles over
-// 8 waves, two per SIMD (half the operand bytes per flop of 128x128, and one
-// wave's waits overlap the other's MFMAs).
+// large float32 products take 256x256 tiles over 8 waves, two per SIMD (half
+// the operand bytes per flop of 128x128, and one wave's waits overlap the
+// other's MFMAs).
 template <typename Tin>
 static hipError_t gemm_dt(const GemmDesc& g, hipStream_t st) {
     if constexpr (sizeof(Tin) == 2) {

@@ -10,17 +10,20 @@
 //     vector address arithmetic (the general kernel spends about 45 vector
 //     and 45 scalar instructions per stage and wave on it);
 //   * a stage row is 128 bytes of k: whole cache lines.  64-byte rows issue
-//     twice the L2 requests (fc2 278 against 254 us, same tile);
+//     twice the L2 requests (the dense fc2 278 against 254 us with the tile of
+//     that time);
 //   * the fragments of the next k step are read while the current step's
 //     MFMAs run, across the stage barrier too;
 //   * the MFMAs read B's rows in a permuted order (gb_col_of_slot), so a lane
 //     ends with 8 consecutive columns per half tile; the rows are rounded,
 //     staged through LDS and stored as whole 64- or 128-byte row pieces, past
-//     the L2 for large outputs: partial-line stores cost fc1 + GELU 316
-//     against 304 us, and z that is written back through the L2 another 20 us
-//     (282 us with streaming stores).
-// fc1 + GELU (50432 x 3072 x 768) takes 280 us here against 391 with the
-// general kernel, the dense fc2 (50432 x 768 x 3072) 220 against 288.
+//     the L2 for large outputs: on the 320 x 256 tile, partial-line stores cost
+//     fc1 + GELU 316 against 304 us, and z that is written back through the L2
+//     another 20 us.
+// In the dense FFN (kernel time, both libraries on one card): fc1 + GELU, 50432
+// x 3072 x 768, 371 us with the general kernel, 287 here (two workgroups on a
+// CU); fc2, 50432 x 768 x 3072, 294 and 229 (320 x 256); at 25216 rows 183 and
+// 148, 166 and 110.
 #pragma once
 
 #include "kernels.h"
@@ -241,7 +244,8 @@ __device__ __forceinline__ void gb_zero(f32x16 (&acc)[TM][TN]) {
 // Bias of column nw + lane (nw: the wave's first column; 0 past N or without a
 // bias), loaded before the k loop and added after it: a register a lane in
 // between.  An accumulator that starts at the bias rounds every partial sum
-// at the bias's magnitude.
+// at the bias's magnitude, and takes four times as many loads (1576 tokens,
+// top-1, D = 768: the layer's three products 5 us more).
 __device__ __forceinline__ float gb_bias(const GemmDesc& g, int nw, int lane) {
     const __amdgpu_buffer_rsrc_t rb = raw_rsrc(g.bias, g.bias != nullptr ? static_cast<int64_t>(g.N) * 4 : 0);
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, (nw + lane) * 4, 0, 0));
@@ -546,8 +550,11 @@ void k_gemm_bf16(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
 // fragments in registers: the LDS of B and of A's upper half is free as soon
 // as phase 0 starts, that of the lower half when phase 1 does, so the loads of
 // stage kt + 2 are issued one and a half to two stages before they are read
-// (one with the kernel above): 50432 x 768 x 3072 246 -> 226 us, 65536 x 1024
-// x 8192 902 -> 839 us (1310 TFLOP/s).
+// (one with the kernel above: 902 us for 65536 x 1024 x 8192 on a 256 x 256
+// tile of it).  Against the 320 x 256 tile: 65536 x 1024 x 8192 827 and 1066
+// us (1330 TFLOP/s), 50432 x 384 x 1536 80 and 103, 50432 x 768 x 3072 234 and
+// 232, 25216 x 768 x 3072 139 and 110: what the tiles leave of the last round
+// decides.
 template <int EPI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_bf16_long(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
@@ -699,8 +706,9 @@ void k_gemm_bf16_long(GemmDesc g, int mtiles, int ntiles, int group, int nt_stor
 // them, here one workgroup's epilogue runs beside the other's MFMAs.  80 KB of
 // LDS each: A has two stage buffers, B one, which is free as soon as its
 // fragments (a whole stage's, read first) are in registers.
-// 50432 x 3072 x 768 320 -> 268 us, 50432 x 1536 x 384 111 -> 93, 25216 x 3072
-// x 768 149 -> 138.
+// Against the better of the tiles above, in the dense FFN: 50432 x 3072 x 768
+// 322 and 288 us, 50432 x 1536 x 384 115 and 100, 25216 x 3072 x 768 160 and
+// 150.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_bf16_duo(GemmDesc g, int mtiles, int ntiles, int group, int nt_store) {
     constexpr int SB = kGbRow, BM = 256, BN = 128, CPR = 8, BK = 64, TM = 4, TN = 2, AL = 8, BL = 4;
