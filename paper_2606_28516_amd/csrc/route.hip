@@ -246,8 +246,8 @@ void k_route(
     const int rows = static_cast<int>(T - tile0 < kTile ? T - tile0 : kTile);
     const __amdgpu_buffer_rsrc_t rx = raw_rsrc(x + tile0 * D, static_cast<int64_t>(rows) * D * esz);
     const __amdgpu_buffer_rsrc_t rw = raw_rsrc(Wg, static_cast<int64_t>(E) * D * esz);
-    __shared__ double bgv[EP];                       // router bias, loaded up front (read
     for (int i = blockIdx.x * 256 + tid; i < nzero; i += gridDim.x * 256) zero[i] = 0;
+    __shared__ double bgv[EP];                       // router bias, loaded up front (read
     if (tid < EP)                                    // after the barrier past the transposes)
         bgv[tid] = (bg != nullptr && tid < E) ? static_cast<double>(bg[tid]) : 0.0;
 
